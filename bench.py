@@ -51,7 +51,7 @@ def quant_bytes(rows: int, K: int, split) -> int:
     return rows * K * 2 + rows * (p4 // 2 + 3 * p6 // 4 + p8) + rows * K // 32 + 4 * K
 
 
-DIRECT_MAX_M = 64  # mm_gemm takes the HBM-bound decode kernel up to this many activation rows
+DIRECT_MAX_M = 64  # up to this many activation rows mm_gemm is bound by the weight stream from HBM
 
 
 def gemm_bytes(M: int, N: int, K: int, split) -> int:
@@ -65,7 +65,8 @@ def gemm_bytes(M: int, N: int, K: int, split) -> int:
 # sources each GEMM kernel is compiled from (a committed counter summary is
 # used only while they are unchanged)
 GEMM_SOURCES = {"tiled": ("gemm_tiled.hip", "gemm_common.hpp", "mx_device.hpp", "kernels.hpp"),
-                "direct": ("gemm_direct.hip", "gemm_common.hpp", "mx_device.hpp", "kernels.hpp")}
+                "direct": ("gemm_direct.hip", "gemm_split.hip", "gemm_common.hpp", "mx_device.hpp",
+                           "kernels.hpp")}
 CALIB_BYTES = 256 << 20  # plain copy used to calibrate the FETCH_SIZE / WRITE_SIZE counters
 
 

@@ -18,8 +18,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmicromix.so")
-SOURCES = ["api.cpp", "quantize.hip", "gemm_direct.hip", "gemm_tiled.hip", "calibrate.hip"]
-OPT = {"gemm_tiled.hip": "-O2"}  # default -O3
+SOURCES = ["api.cpp", "quantize.hip", "gemm_direct.hip", "gemm_split.hip", "gemm_tiled.hip", "calibrate.hip"]
+OPT = {"gemm_tiled.hip": "-O2", "gemm_split.hip": "-O2"}  # default -O3
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -14,9 +14,15 @@ namespace {
 
 constexpr int64_t kMaxQuantK = 32768;  // one row of bf16 must fit the LDS budget
 constexpr int64_t kMaxRows = (int64_t)1 << 31;
-// Up to this many activation rows the GEMM streams operands straight from
-// global memory (memory-bound decode); above it the LDS-tiled kernel runs.
-constexpr int64_t kDirectMaxM = 64;
+// Up to this many activation rows (one 16-row tile) the decode kernel may run.
+constexpr int64_t kDirectMaxM = 16;
+// ... unless the weight is larger than this and not mostly 8-bit codes: the
+// K-splitting kernel streams long weights faster (us, 8 rows, decode kernel
+// against it: 28672 x 4096 mixed, 71 MB, 15.7 / 12.7, E2M1 62 MB 12.9 / 11.4;
+// 5120 x 27648 mixed, 86 MB, 23.0 / 18.4), the decode kernel the short ones
+// (14336 x 4096 mixed, 36 MB, 8.2 / 8.1; 4096 x 4096, 10 MB, 4.4 / 4.7) and
+// E4M3 (28672 x 4096, 21.3 / 23.5; 5120 x 27648, 34 / 38).
+constexpr int64_t kDirectMaxWeight = 40ll << 20;
 // Calibration workspace: the workgroup maxima (nchunks * tiles <= 256 words)
 // and the per-block group counts (2 * K / 256 <= 256 words), then fp64
 // partial sums and means, then int32 per-slice rank counts.
@@ -174,7 +180,35 @@ mm::Operand operand(const mm_mx_tensor* t) {
   return o;
 }
 
+hipError_t launch_gemm(const mm::GemmArgs& g, const Layout& w, hipStream_t s) {
+  const int64_t bytes = w.bytes[0] + w.bytes[1] + w.bytes[2];
+  if (g.x.rows <= kDirectMaxM && (bytes <= kDirectMaxWeight || 2 * w.bytes[2] > bytes))
+    return mm::launch_gemm_direct(g, s);
+  int shape = -1;
+  hipError_t e = mm::choose_gemm_split(g, &shape);
+  if (e != hipSuccess) return e;
+  return shape >= 0 ? mm::launch_gemm_split(g, shape, s) : mm::launch_gemm_tiled(g, s);
+}
+
 }  // namespace
+
+namespace mm {
+
+hipError_t device_cus(int* cus) {
+  thread_local int last_dev = -1, last_cus = 0;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev != last_dev) {
+    e = hipDeviceGetAttribute(&last_cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    last_dev = dev;
+  }
+  *cus = last_cus;
+  return hipSuccess;
+}
+
+}  // namespace mm
 
 extern "C" {
 
@@ -219,7 +253,7 @@ mm_status mm_gemm(const mm_mx_tensor* a, const mm_mx_tensor* w, void* y_bf16, in
   g.ldy = ldy;
   g.fs = format_set(a);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = a->rows <= kDirectMaxM ? mm::launch_gemm_direct(g, s) : mm::launch_gemm_tiled(g, s);
+  hipError_t e = launch_gemm(g, layout(w->rows, w->split), s);
   if (e != hipSuccess) return fail(MM_ERR_DEVICE, "mm_gemm: launch failed: %s", hipGetErrorString(e));
   return MM_OK;
 }

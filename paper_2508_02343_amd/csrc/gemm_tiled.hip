@@ -716,21 +716,6 @@ static hipError_t launch_tile(const GemmArgs& a, hipStream_t stream) {
   return hipErrorInvalidValue;
 }
 
-// CUs of the current device (cached per thread for the last device).
-static hipError_t device_cus(int* cus) {
-  thread_local int last_dev = -1, last_cus = 0;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev != last_dev) {
-    e = hipDeviceGetAttribute(&last_cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    last_dev = dev;
-  }
-  *cus = last_cus;
-  return hipSuccess;
-}
-
 hipError_t launch_gemm_tiled(const GemmArgs& a, hipStream_t stream) {
   // 256 x 256 tiles when they give every CU at least one, else 256 x 128
   // (twice the tiles)

@@ -722,21 +722,6 @@ static hipError_t launch_pipelined(const QuantArgs& a, int rpp, int T, size_t ld
   return hipGetLastError();
 }
 
-// CUs of the current device (cached per thread for the last device).
-static hipError_t device_cus(int* cus) {
-  thread_local int last_dev = -1, last_cus = 0;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev != last_dev) {
-    e = hipDeviceGetAttribute(&last_cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    last_dev = dev;
-  }
-  *cus = last_cus;
-  return hipSuccess;
-}
-
 template <int NPER, bool kNorm>
 static hipError_t launch_ring_n(const QuantArgs& a, int rpp, int row_stride, int slot_stride, int grid,
                                 hipStream_t stream) {

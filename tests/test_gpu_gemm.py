@@ -160,6 +160,55 @@ def test_prefill_configs_sampled(w):
     assert_gemm_close(y_to_f64(y[torch.from_numpy(rows).cuda()])[:, cols], O.gemm_mixed(ra, rw), ctx=w.name)
 
 
+@pytest.mark.parametrize("split", [(320, 256, 128), (704, 0, 0), (32, 672, 0), (0, 96, 608)], ids=str)
+@pytest.mark.parametrize("M,N", [(17, 33), (32, 4100), (20, 9000), (33, 31), (65, 1003), (129, 2050), (192, 5500),
+                                 (250, 4097)])
+def test_split_k_tiles(M, N, split):
+    """The K-splitting kernel between the decode and the tiled one: its tile
+    shapes (32 or 64 weight rows by 32 to 128 activation rows, chosen by size),
+    last tiles that reach back into the tile before in both directions,
+    columns that are no multiple of 8, wavefronts without steps, with one and
+    with an odd number of steps.  Every output against the oracle."""
+    note(f"split-K M={M} N={N} split={split}")
+    xb, wb, perm = _rand_case(M, N, split, seed=M + 3 * N + split[0])
+    _check_full(xb, wb, perm, split, f"M{M} N{N} {split}")
+
+
+@pytest.mark.parametrize("formats", [("E3M2", "E4M3"), ("E2M3", "E5M2")], ids="-".join)
+@pytest.mark.parametrize("M,N,split", [(500, 4090, (2304, 576, 192)), (97, 600, (9216, 3328, 1792)),
+                                       (9, 9000, (5120, 1024, 512))], ids=str)
+def test_split_k_long(M, N, split, formats):
+    """The same with many steps per wavefront: the widest tile (64 x 128 at 500
+    rows), odd step counts, and the decode kernel's side of its 40 MB line (9000
+    rows of 6656 channels: 35 MB)."""
+    note(f"split-K long M={M} N={N} split={split} {formats}")
+    xb, wb, perm = _rand_case(M, N, split, seed=M + N)
+    b = _b()
+    p = to_dev_perm(perm)
+    a = b.quantize_act(to_dev_bf16(xb), p, split, formats=formats)
+    w = b.quantize_weight(to_dev_bf16(wb), p, split, formats=formats)
+    y = b.gemm(a, w)
+    torch.cuda.synchronize()
+    fm = (O.E2M1, O.FORMATS[formats[0]], O.FORMATS[formats[1]])
+    ra, rw = O.quantize_mixed(xb, perm, split, fm), O.quantize_mixed(wb, perm, split, fm)
+    assert_gemm_close(y_to_f64(y), O.gemm_mixed(ra, rw), ctx=f"{formats} M{M} N{N}")
+
+
+@pytest.mark.parametrize("M", [1, 16])
+def test_split_k_decode(M):
+    """At most 16 rows against a weight of more than 40 MB that is not mostly
+    8-bit: the K-splitting kernel (256 sampled columns against the oracle)."""
+    N, split = 20000, (3072, 768, 256)
+    note(f"split-K decode M={M}")
+    xb, wb, perm = _rand_case(M, N, split, seed=M)
+    a, wq = _gpu_pair(xb, wb, perm, split)
+    y = _b().gemm(a, wq)
+    torch.cuda.synchronize()
+    cols = np.unique(np.concatenate([[0, N - 1], np.random.default_rng(2).choice(N, 254, replace=False)]))
+    ra, rw = O.quantize_mixed(xb, perm, split), O.quantize_mixed(wb[cols], perm, split)
+    assert_gemm_close(y_to_f64(y)[:, cols], O.gemm_mixed(ra, rw), ctx=f"M{M}")
+
+
 def test_one_activation_feeds_two_weights():
     """One quantised activation reused by two GEMMs with the same sigma."""
     note("shared activation")
