@@ -130,6 +130,7 @@ mm_status quantize(const void* x, int64_t ldx, const int32_t* perm, const mm_mx_
   a.norm = norm ? 1 : 0;
   a.gamma = static_cast<const uint16_t*>(gamma);
   a.eps = eps;
+  a.inv_k = 1.0 / (double)out->K;
   hipError_t e = mm::launch_quantize(a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(MM_ERR_DEVICE, "%s: launch failed: %s", who, hipGetErrorString(e));
   return MM_OK;

@@ -45,6 +45,7 @@ struct QuantArgs {
   int norm;
   const uint16_t* gamma;
   float eps;
+  double inv_k;  // 1 / K
 };
 
 // One quantised GEMM operand.

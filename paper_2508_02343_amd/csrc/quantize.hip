@@ -1,43 +1,49 @@
 // Fused reorder-and-quantize (MicroMix Sec. 3.2 "Quantization kernel",
 // Fig. "micromix-design" b): one pass over bf16 rows that gathers channels by
 // sigma (Sec. 3.1), takes each 32-channel block's shared E8M0 scale and writes
-// E2M1 / E3M2 / E4M3 codes for the three groups (Sec. 2.1 MX rule).
+// E2M1 / E3M2 / E4M3 codes for the three groups (Sec. 2.1 MX rule), with the
+// layer's RMSNorm in front where asked for (App. D.2).
 //
-// HBM-bound design for gfx950, two kernels:
-//  - the ring kernel (passes of two or more rows, K <= 8192; below the
-//    pipelined one): producer wavefronts load each pass straight into an
-//    LDS ring with global_load_lds_dwordx4, several passes in flight per CU,
-//    and with the norm also sum each pass's squares one pass ahead;
-//  - the pipelined kernel, as follows.
-//  - a pass is `rpp` consecutive rows; the grid is sized to the number of
-//    workgroups the chip holds at once, each XCD takes a contiguous range of
-//    passes and its workgroups stride through it; one thread per (row,
-//    32-channel block), so each thread always quantises the same block index
-//    and keeps that block's 32 sigma entries in registers, as LDS byte
-//    addresses, for the whole workgroup;
-//  - rows arrive with 16-byte coalesced loads (the only HBM read) into
-//    registers and are written to one of two LDS stages: the loads of pass
-//    p+1 are in flight while pass p is quantised from the other stage;
-//  - the gather is 32 LDS u16 reads per thread; the block absmax is a packed
-//    16-bit max over the sign-cleared bf16 bits;
+// HBM-bound.  A workgroup stages a pass of RH rows in LDS, one thread per (row,
+// 32-channel block), and several workgroups share a CU, so that one loads
+// while another quantises:
+//  - rows arrive with 16-byte coalesced loads (the only HBM read, four per
+//    thread, all in flight at once, marked non-temporal as they are read once)
+//    and go to LDS; the next pass's loads are issued before this one is
+//    quantised;
+//  - lanes run over the pass's rows first, so the lanes that store one
+//    block's codes hold consecutive rows, whose codes are consecutive in the
+//    packed layout (64-byte runs with four rows);
+//  - each thread keeps its block's 32 sigma entries as byte offsets in a row,
+//    two per register, and gathers with 32 LDS u16 reads; the block absmax is a
+//    packed 16-bit max over the sign-cleared bf16 bits;
 //  - the codes come from the gfx950 scaled conversions, which divide by the
 //    E8M0 scale and round to nearest even (E2M1 and E4M3 two codes per
 //    instruction, E3M2 one instruction per block giving the packed 24-byte bit
 //    stream).  The E4M3 conversion does not saturate, so E4M3 inputs are first
-//    clamped to 448 * scale, which is exact in bf16;
-//  - consecutive lanes own consecutive blocks, so a wavefront's code stores
-//    cover a contiguous span of each group.
+//    clamped to 448 * scale, which is exact in bf16.
 //
-// With the RMSNorm fused in front (the norm variant, App. D.2): the waves
-// sum each staged row's squares in fp64 (a row split across several waves),
-// every thread forms its row's factor r = fp32(1 / sqrt(mean(x^2) + eps)),
-// and every gathered element becomes bf16(gamma * bf16(x * r)) (fp32
-// products, round to nearest even) before the block absmax.  The weights in
-// block order (gamma gathered by sigma) sit in LDS, four 16-byte pieces per
-// block at (piece * nblk + block) * 16 so a wavefront's reads are
-// conflict-free, in the unused tail of stage 0 when it has room; otherwise
-// (one wide row per pass) each thread keeps its block's 32 weights in
-// registers.
+// With the RMSNorm, each thread also adds up the squares of the values it
+// loads, in fp64 (exact squares, so no scaling is needed), before they go to
+// LDS; the wavefronts' row sums meet in LDS under the same barrier as the
+// rows, and every gathered element becomes bf16(gamma * bf16(x * r)) (fp32
+// products, round to nearest even).  The weights sit in LDS in block order,
+// four 16-byte pieces per block at (piece * nblk + block) * 16, so a
+// wavefront's reads are conflict-free.
+//
+// Measured (us; before: a ring of LDS slots filled by producer wavefronts, one
+// workgroup per CU, and for K > 8192 one row per workgroup at a time):
+//   plain   8 x 4096   5.2 -> 3.7    2048 x 4096  9.3 ->  8.5   8192 x 5120   30.7 -> 25.1 (4.4 TB/s)
+//         333 x 27648 19.4 -> 13.3   4096 x 14336 39.5 -> 34.0   5120 x 27648 170  -> 86
+//   norm    8 x 4096   8.6 -> 5.2    2048 x 4096 13.8 -> 12.8   8192 x 5120   43.4 -> 41.4
+//         512 x 4096   9.1 -> 6.5    4096 x 14336 73.3 -> 50.4   5120 x 27648 577  -> 113
+// The plain kernel waits on memory (loads in flight only while a workgroup
+// quantises, code stores in runs of a few rows); the norm's 540 VALU
+// instructions per wavefront and pass, against 190, bound its large shapes.
+// What spills costs more than what it saves: 128 registers hold the norm
+// variant only because it gathers eight channels at a time (with 32 spilled
+// registers 8192 x 5120 took 59 us, with 10, 44).  Tried: two blocks per thread
+// (34 us plain on 8192 x 5120), five wavefronts per SIMD (spills, 37 us).
 #include "kernels.hpp"
 
 namespace mm {
@@ -50,16 +56,6 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef int i32x6 __attribute__((ext_vector_type(6)));
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// The second LDS stage sits at a fixed byte offset, so stage selection folds
-// into the immediate offset of the LDS reads.  One stage holds at most this
-// many bytes (rpp * K * 2).
-constexpr int kStageOff = 32768;
-constexpr int kMaxChunks = 4;  // 16-byte loads per thread per pass
-constexpr int kMaxRowSlots = 256;  // row square sums of one pass (rows per pass, or waves, never exceed this)
-// dynamic LDS at most: two stages, the dummy slot and the row square sums; or
-// one 64 KB row, the dummy slot, 16 (row, part) sums and its 64 KB of weights
-constexpr int kMaxLds = 2 * (2 * kStageOff) + 16 + 8 * 16;
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
@@ -101,58 +97,32 @@ __device__ __forceinline__ void zero_tail(const QuantArgs& a, int64_t step, int6
   for (int jj = j + 1; jj < kStepBlocks; ++jj) zero_block<G>(a, step, gstep, n, jj);
 }
 
-// Quantise block b (local to its group) of row n from the LDS stage at byte
-// offset `off` from the addresses; rows past a.rows are padding and quantise
-// an all-zero block.  The thread that owns a group's last block also zeroes
-// the padding blocks of that step.
-template <bool kNorm>
-__device__ __forceinline__ void quantize_block(const uint32_t (&addr)[32], uint32_t off, int group, bool last,
-                                               const QuantArgs& a, int64_t n, int b, int gstep0,
-                                               const uint32_t (&gpk)[16], float rn) {
-  // gather: the block's 32 permuted channels, all reads issued before any
-  // is used, then packed as 16 bf16 pairs
-  uint16_t e[32];
-#pragma unroll
-  for (int i = 0; i < 32; ++i) e[i] = lds_u16(addr[i] + off);
-  __builtin_amdgcn_sched_barrier(0);
-  uint32_t d[16];
+// Bytes from row 0's codes of a block to row n's, n a multiple of the rows per
+// pass: whole row groups, then rows within one.
+template <int G>
+__device__ __forceinline__ int64_t row_offset(int64_t n) {
+  return (n & ~(int64_t)(kRowGroup - 1)) * step_row_bytes(G) + (n & (kRowGroup - 1)) * (G == 1 ? 24 : 16);
+}
+
+// Quantise the 32 gathered channels d (bf16 pairs) of block b (local to its
+// group) of row n = n0 + prow, n0 uniform over the workgroup; dst and sdst are
+// the block's codes and scale byte of row prow.  Rows past a.rows are padding
+// and quantise an all-zero block.  The thread that owns a group's last block
+// also zeroes the padding blocks of that step.
+__device__ __forceinline__ void encode_block(uint32_t (&d)[16], int group, bool last, const QuantArgs& a, int64_t n0,
+                                             int prow, int b, int gstep0, uint8_t* dst, uint8_t* sdst) {
+  const int64_t n = n0 + prow;
   const bool pad_row = n >= a.rows;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    u16x2 v;
-    v.x = e[2 * i];
-    v.y = e[2 * i + 1];
-    d[i] = __builtin_bit_cast(uint32_t, v);
-  }
-  if constexpr (kNorm) {
-    // bf16(gamma * bf16(x * r)): fp32 products, each rounded to nearest even;
-    // four pairs at a time, so the temporaries of all sixteen are never live
-    // together
-#pragma unroll
-    for (int i0 = 0; i0 < 16; i0 += 4) {
-#pragma unroll
-      for (int i = i0; i < i0 + 4; ++i) {
-        const uint32_t w = d[i];
-        const f32x2 t = {__uint_as_float(w << 16) * rn, __uint_as_float(w & 0xFFFF0000u) * rn};
-        const uint32_t y = __builtin_bit_cast(uint32_t, __builtin_convertvector(t, bf16x2));
-        const f32x2 u = {__uint_as_float(y << 16) * __uint_as_float(gpk[i] << 16),
-                         __uint_as_float(y & 0xFFFF0000u) * __uint_as_float(gpk[i] & 0xFFFF0000u)};
-        d[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(u, bf16x2));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
 #pragma unroll
   for (int i = 0; i < 16; ++i) d[i] = pad_row ? 0u : d[i];
 
   // absmax: bf16 magnitudes compare as unsigned integers
-  uint32_t m[16];
+  uint32_t m[4];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) m[i] = d[i] & 0x7FFF7FFFu;
+  for (int i = 0; i < 4; ++i) m[i] = d[i] & 0x7FFF7FFFu;
 #pragma unroll
-  for (int s = 8; s >= 1; s >>= 1)
-#pragma unroll
-    for (int i = 0; i < s; ++i) m[i] = max_u16x2(m[i], m[i + s]);
+  for (int i = 4; i < 16; ++i) m[i & 3] = max_u16x2(m[i & 3], d[i] & 0x7FFF7FFFu);
+  m[0] = max_u16x2(max_u16x2(m[0], m[1]), max_u16x2(m[2], m[3]));
   const uint32_t amax = (m[0] & 0xFFFFu) > (m[0] >> 16) ? (m[0] & 0xFFFFu) : (m[0] >> 16);
 
   // Shared exponent e = floor(log2 amax) - emax, clamped below at -127: for
@@ -168,6 +138,7 @@ __device__ __forceinline__ void quantize_block(const uint32_t (&addr)[32], uint3
   const int64_t step = b >> 2;
   const int j = b & 3;
   const int64_t gstep = gstep0 + step;
+  sdst[n0 * kStepBlocks] = (uint8_t)sbyte;
   if (group == 0) {
     uint32_t w[4];
 #pragma unroll
@@ -179,7 +150,7 @@ __device__ __forceinline__ void quantize_block(const uint32_t (&addr)[32], uint3
       v = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(v, __builtin_bit_cast(bf16x2, d[4 * q + 3]), scale, 3);
       w[q] = v;
     }
-    *reinterpret_cast<uint4*>(a.q[0] + code_offset<0>(step, a.rp, n, j)) = make_uint4(w[0], w[1], w[2], w[3]);
+    *reinterpret_cast<uint4*>(dst + row_offset<0>(n0)) = make_uint4(w[0], w[1], w[2], w[3]);
     if (last) zero_tail<0>(a, step, gstep, n, j);
   } else if (group == 1) {
     u32x16 v;
@@ -198,10 +169,10 @@ __device__ __forceinline__ void quantize_block(const uint32_t (&addr)[32], uint3
       for (int i = 0; i < 16; ++i) v[i] = d[i];
       c = __builtin_amdgcn_cvt_scalef32_pk32_bf6_bf16(__builtin_bit_cast(bf16x32, v), scale);
     }
-    uint2* dst = reinterpret_cast<uint2*>(a.q[1] + code_offset<1>(step, a.rp, n, j));
-    dst[0] = make_uint2((uint32_t)c[0], (uint32_t)c[1]);
-    dst[1] = make_uint2((uint32_t)c[2], (uint32_t)c[3]);
-    dst[2] = make_uint2((uint32_t)c[4], (uint32_t)c[5]);
+    uint2* p = reinterpret_cast<uint2*>(dst + row_offset<1>(n0));
+    p[0] = make_uint2((uint32_t)c[0], (uint32_t)c[1]);
+    p[1] = make_uint2((uint32_t)c[2], (uint32_t)c[3]);
+    p[2] = make_uint2((uint32_t)c[4], (uint32_t)c[5]);
     if (last) zero_tail<1>(a, step, gstep, n, j);
   } else {
     // the largest finite value times 2^e in bf16, mantissa 0x60 (1.75): E4M3
@@ -224,309 +195,125 @@ __device__ __forceinline__ void quantize_block(const uint32_t (&addr)[32], uint3
       }
       w[q] = __builtin_bit_cast(uint32_t, v);
     }
-    uint8_t* dst = a.q[2] + code_offset<2>(step, a.rp, n, j);
-    *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
-    *reinterpret_cast<uint4*>(dst + 512) = make_uint4(w[4], w[5], w[6], w[7]);
+    uint8_t* p = dst + row_offset<2>(n0);
+    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    *reinterpret_cast<uint4*>(p + 512) = make_uint4(w[4], w[5], w[6], w[7]);
     if (last) zero_tail<2>(a, step, gstep, n, j);
   }
-  a.sc[(gstep * a.rp + n) * kStepBlocks + j] = (uint8_t)sbyte;
+}
+
+// base + one 16-bit half of w (one instruction; written out because the
+// compiler would otherwise hoist the 32 halves, or their sums, out of the
+// loop over the passes and spill).
+template <int H>
+__device__ __forceinline__ uint32_t add_word(uint32_t base, uint32_t w) {
+  uint32_t r;
+  if constexpr (H == 0)
+    asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+        : "=v"(r)
+        : "v"(base), "v"(w));
+  else
+    asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+        : "=v"(r)
+        : "v"(base), "v"(w));
+  return r;
+}
+
+// v + (v of another lane of the row of 16, chosen by the DPP control).
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+  return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Sum over the wavefront of each of N (1, 2 or 4) values per lane: lane l gets
+// the sum of value l % N, in a fixed order.  The first steps, over lanes 1 and
+// 2 apart, halve the values; the others rotate within rows of 16 lanes and
+// swap rows, so nothing goes through LDS.
+template <int N>
+__device__ __forceinline__ double wave_sums(const double (&v)[N], int lane) {
+  constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kRor4 = 0x124, kRor8 = 0x128;  // quad_perm / row_ror
+  double t;
+  if constexpr (N == 4) {
+    // lane l keeps the values of its own parity of l / 2, then of l
+    double k[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const double a = add_dpp<kXor2>(v[i]), b = add_dpp<kXor2>(v[i + 2]);
+      k[i] = lane & 2 ? b : a;
+    }
+    const double a = add_dpp<kXor1>(k[0]), b = add_dpp<kXor1>(k[1]);
+    t = lane & 1 ? b : a;
+  } else if constexpr (N == 2) {
+    const double a = add_dpp<kXor1>(v[0]), b = add_dpp<kXor1>(v[1]);
+    t = add_dpp<kXor2>(lane & 1 ? b : a);
+  } else {
+    t = add_dpp<kXor2>(add_dpp<kXor1>(v[0]));
+  }
+  t = add_dpp<kRor8>(add_dpp<kRor4>(t));
+  // rows of 16: swapping a copy's odd rows with another's even rows pairs
+  // them up, then the halves
+  uint64_t u = __builtin_bit_cast(uint64_t, t);
+  const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  t = __builtin_bit_cast(double, (uint64_t)h16[0] << 32 | l16[0]) + __builtin_bit_cast(double, (uint64_t)h16[1] << 32 | l16[1]);
+  u = __builtin_bit_cast(uint64_t, t);
+  const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  return __builtin_bit_cast(double, (uint64_t)h32[0] << 32 | l32[0]) + __builtin_bit_cast(double, (uint64_t)h32[1] << 32 | l32[1]);
+}
+
+// fp32(1 / sqrt(m)), m > 0 and normal, evaluated in fp64: the hardware's
+// reciprocal square root estimate and two Newton steps (relative error below
+// 2^-51, as a square root and a division have) instead of their
+// long expansions, which every thread of a row would run.
+__device__ __forceinline__ float rsqrt_f64(double m) {
+  double y = __builtin_amdgcn_rsq(m);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) y = fma(y * 0.5, fma(-m * y, y, 1.0), y);
+  return (float)y;
+}
+
+// 32-bit LDS addresses
+template <typename T>
+__device__ __forceinline__ T lds_load(uint32_t addr) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) T*>((uintptr_t)addr);
+}
+template <typename T>
+__device__ __forceinline__ void lds_store(uint32_t addr, T v) {
+  *reinterpret_cast<__attribute__((address_space(3))) T*>((uintptr_t)addr) = v;
 }
 
 }  // namespace
 
-// Launch shape: blockDim.x = roundup64(rpp * nblk) <= kMaxThreads threads;
-// thread t owns pass-row t / nblk and block t % nblk; gridDim.x <= number of
-// passes.  kPipe: two LDS stages of rpp * K * 2 <= kStageOff bytes, loads of
-// the next pass overlap the current one; otherwise gridDim.x equals the
-// number of passes and one stage holds up to 2 * kStageOff bytes.
-// Sums of squares of the rpp rows staged at byte offset stage_off, spread
-// over the workgroup's W waves: with rpp <= W each row gets W / rpp waves,
-// each summing one contiguous part of it; otherwise each wave sums whole rows
-// (rows strided by W).  Every (row, part) sum goes to slot
-// row * row_parts(rpp, W) + part at sq_off; squares of bf16 values are exact
-// in fp64, and the sums use four accumulators per lane and a fixed shuffle
-// tree, so the result does not depend on timing.
-__device__ __forceinline__ int row_parts(int rpp, int W) { return rpp <= W ? W / rpp : 1; }
+constexpr int kMaxThreads = 1024;
 
-__device__ __forceinline__ void row_square_sums(const u32x4* lds4, uint32_t stage_off, uint32_t sq_off, int rpp, int K) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
-  const int chunks = K >> 3;
-  const int parts = row_parts(rpp, W);
-  const int first = rpp <= W ? wave / parts : wave;
-  const int step = rpp <= W ? rpp : W;  // loop once when rows get several waves
-  for (int pr = first; pr < rpp; pr += step) {
-    const int part = rpp <= W ? wave % parts : 0;
-    const int c0 = part * chunks / parts, c1 = (part + 1) * chunks / parts;
-    const u32x4* row = lds4 + ((stage_off + (uint32_t)pr * K * 2) >> 4);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int c = c0 + lane; c < c1; c += 64) {
-      const u32x4 v = row[c];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const double lo = (double)__uint_as_float(v[k] << 16), hi = (double)__uint_as_float(v[k] & 0xFFFF0000u);
-        acc[k] += lo * lo;
-        acc[k] += hi * hi;
-      }
-    }
-    double s = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) reinterpret_cast<__attribute__((address_space(3))) double*>((uintptr_t)sq_off)[pr * parts + part] = s;
-    if (rpp <= W) break;
-  }
-}
-
-// fp32 row factor of pass-row pr from its part sums (after a barrier): the
-// same operations, in the same order, in every thread of the row.
-__device__ __forceinline__ float row_factor(uint32_t sq_off, int pr, int rpp, int K, float eps) {
-  const int parts = row_parts(rpp, blockDim.x >> 6);
-  const __attribute__((address_space(3))) double* sq =
-      reinterpret_cast<const __attribute__((address_space(3))) double*>((uintptr_t)sq_off) + pr * parts;
-  double s = sq[0];
-  for (int k = 1; k < parts; ++k) s += sq[k];
-  return (float)(1.0 / sqrt(s / (double)K + (double)eps));
-}
-
-// kNorm: 0 plain; 1 RMSNorm with the weights in registers; 2 RMSNorm with the
-// block-order weights in LDS at byte offset gamma_off.
-template <int kMaxThreads, bool kPipe, int kNorm>
-__global__ __launch_bounds__(kMaxThreads) void quantize_rows_kernel(QuantArgs a, int rpp, int gamma_off) {
-  extern __shared__ u32x4 lds4[];
+// Pass p covers rows p RH .. p RH + RH - 1 (padding rows included), thread t
+// block t / RH of row t % RH; gridDim.x <= passes.  LDS: RH rows of 2 K + 16
+// bytes (the padding shifts the banks of consecutive rows), then with the norm
+// 2 K bytes of weights and RH fp64 sums per wavefront.
+template <int RH, bool kNorm>
+__global__ __launch_bounds__(kMaxThreads) void quantize_kernel(QuantArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t stage[];
+  static_assert(RH <= 4 || !kNorm, "a row sum's chunks belong to one row per load");
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)stage;
+  const int K = a.K, nblk = K >> 5;
   const int tid = threadIdx.x;
-  const int T = blockDim.x;
-  const int K = a.K;
-  const int nblk = K >> 5;
-  const int prow = tid / nblk;
-  const int blk = tid - prow * nblk;
-  const bool active = prow < rpp;
-  const int stage_bytes = rpp * K * 2;
-  const int nchunks = stage_bytes >> 4;  // 16-byte chunks per pass
-  const int64_t passes = (a.rp + rpp - 1) / rpp;  // padding rows included
+  const int n_act = RH * nblk;  // threads with a block
+  const bool active = tid < n_act;
+  const int t = active ? tid : 0;
+  const int blk = t / RH, prow = t - blk * RH;
+  const uint32_t row_stride = (uint32_t)(2 * K + 16);
+  const uint32_t gam0 = lds0 + RH * row_stride;
+  const uint32_t sums0 = gam0 + 2u * (uint32_t)K;
 
-  // sigma of this thread's block as LDS byte addresses within a stage; an
-  // out-of-range entry (a caller error) is clamped to stay inside the row
-  uint32_t addr[32];
-  const int base = (int)(uint32_t)(uintptr_t)lds4 + (active ? prow : 0) * K * 2;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int4 v = *reinterpret_cast<const int4*>(a.perm + (active ? blk : 0) * 32 + 4 * q);
-    const int p[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) addr[4 * q + i] = (uint32_t)(base + 2 * ((unsigned)p[i] < (unsigned)K ? p[i] : 0));
-  }
-  // keep the full addresses in registers: otherwise the common base is
-  // factored out and re-added before every LDS read
-#pragma unroll
-  for (int i = 0; i < 32; ++i) asm volatile("" : "+v"(addr[i]));
-  // the norm weights of this thread's block, gathered by sigma, as bf16 pairs
-  // (kNorm 2: written once to LDS by the threads of pass-row 0)
-  uint32_t gpk[16];
-  if constexpr (kNorm != 0) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int4 v = *reinterpret_cast<const int4*>(a.perm + (active ? blk : 0) * 32 + 4 * q);
-      const int p[4] = {v.x, v.y, v.z, v.w};
-      uint32_t g[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) g[i] = a.gamma[(unsigned)p[i] < (unsigned)K ? p[i] : 0];
-      gpk[2 * q] = g[0] | (g[1] << 16);
-      gpk[2 * q + 1] = g[2] | (g[3] << 16);
-    }
-    if constexpr (kNorm == 2) {
-      if (active && prow == 0)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          lds4[(gamma_off >> 4) + q * nblk + blk] = u32x4{gpk[4 * q], gpk[4 * q + 1], gpk[4 * q + 2], gpk[4 * q + 3]};
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) gpk[i] = 0u;
-  }
-  const int group = blk < a.nb[0] ? 0 : (blk < a.nb[0] + a.nb[1] ? 1 : 2);
-  const int b = blk - (group >= 1 ? a.nb[0] : 0) - (group >= 2 ? a.nb[1] : 0);  // block within its group
-  const int gstep0 = (group >= 1 ? a.steps[0] : 0) + (group >= 2 ? a.steps[1] : 0);
-  const bool last = b == (group == 0 ? a.nb[0] : (group == 1 ? a.nb[1] : a.nb[2])) - 1;  // the group's last block
-
-  // 16-byte chunk c of a pass lies in pass-row c / (K/8); rows past the end
-  // are read from the last row (their results are never stored) and chunks
-  // past the pass go to a 16-byte dummy slot after the stages, so every load
-  // and LDS write is unconditional and in bounds
-  const int chunks_per_row = K >> 3;
-  const uint32_t dummy = (uint32_t)((kPipe ? kStageOff : 0) + stage_bytes);
-  // row square sums of the pass being quantised (norm variant), after the dummy slot
-  const uint32_t sq_off = (uint32_t)(uintptr_t)lds4 + dummy + 16;
-  u32x4 buf[kMaxChunks];
-#define MM_LOAD_PASS(P)                                                                              \
-  {                                                                                                  \
-    const int64_t r0_ = (int64_t)(P)*rpp;                                                            \
-    _Pragma("unroll") for (int j = 0; j < kMaxChunks; ++j) {                                         \
-      int c = tid + j * T;                                                                           \
-      c = c < nchunks ? c : nchunks - 1;                                                             \
-      const int r = c / chunks_per_row;                                                              \
-      int64_t row = r0_ + r;                                                                         \
-      row = row < a.rows ? row : a.rows - 1;                                                         \
-      buf[j] = *reinterpret_cast<const u32x4*>(a.x + row * a.ldx + (int64_t)(c - r * chunks_per_row) * 8); \
-    }                                                                                                \
-  }
-#define MM_STORE_PASS(STAGE)                                                                         \
-  {                                                                                                  \
-    _Pragma("unroll") for (int j = 0; j < kMaxChunks; ++j) {                                         \
-      const int c = tid + j * T;                                                                     \
-      const uint32_t off = c < nchunks ? (uint32_t)((STAGE)*kStageOff + c * 16) : dummy;            \
-      lds4[off >> 4] = buf[j];                                                                       \
-    }                                                                                                \
-  }
-
-  // Workgroups are dealt to the 8 XCDs round-robin; each XCD takes a
-  // contiguous range of passes, so the rows of one 32-row group (which share
-  // cache lines in the packed layout) are written through one XCD's L2.
-  int64_t q, q_end, stride;
-  if (gridDim.x % 8 == 0) {
-    const int x = blockIdx.x & 7;
-    q = passes * x / 8 + (blockIdx.x >> 3);
-    q_end = passes * (x + 1) / 8;
-    stride = gridDim.x / 8;
-  } else {
-    q = blockIdx.x;
-    q_end = passes;
-    stride = gridDim.x;
-  }
-  MM_LOAD_PASS(q);
-  MM_STORE_PASS(0);
-  __syncthreads();
-  for (int i = 0; q < q_end; ++i, q += stride) {
-    const bool more = kPipe && q + stride < q_end;
-    if (more) MM_LOAD_PASS(q + stride);
-    float rn = 0.0f;
-    if constexpr (kNorm != 0) {
-      row_square_sums(lds4, (uint32_t)((i & 1) * kStageOff), sq_off, rpp, K);
-      __syncthreads();
-      rn = row_factor(sq_off, active ? prow : 0, rpp, K, a.eps);
-    }
-    const int64_t row = q * rpp + prow;
-    if (active && row < a.rp) {
-      uint32_t gq[16];
-      if constexpr (kNorm == 2) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const u32x4 v = lds4[(gamma_off >> 4) + k * nblk + blk];
-          gq[4 * k] = v[0];
-          gq[4 * k + 1] = v[1];
-          gq[4 * k + 2] = v[2];
-          gq[4 * k + 3] = v[3];
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) gq[k] = gpk[k];
-      }
-      if ((i & 1) == 0)
-        quantize_block<kNorm != 0>(addr, 0u, group, last, a, row, b, gstep0, gq, rn);
-      else
-        quantize_block<kNorm != 0>(addr, (uint32_t)kStageOff, group, last, a, row, b, gstep0, gq, rn);
-    }
-    if (more) MM_STORE_PASS((i + 1) & 1);
-    __syncthreads();
-  }
-#undef MM_LOAD_PASS
-#undef MM_STORE_PASS
-}
-
-// ---------------------------------------------------------------------------
-// Ring variant (K <= 8192): one workgroup per CU, persistent over
-// a range of passes.  Four producer wavefronts move each pass's rows from HBM
-// straight into an LDS slot with global_load_lds_dwordx4 (1 KB per wavefront
-// instruction, no register staging); a ring of kRingSlots slots keeps up to
-// kRingSlots - 1 passes, about 96 KB per CU, in flight, where the pipelined
-// kernel above has at most one pass of register-staged loads per workgroup.
-// Eight consumer wavefronts quantise exactly as above (thread t owns
-// pass-row t / nblk and block t % nblk).  One s_barrier per pass hands a
-// landed slot to the consumers and the slot they have finished back to the
-// producers.  Only the producers load and only the consumers store, so each
-// producer's vmcnt counts its own loads alone and the wait for a pass is one
-// constant: every producer issues NPER loads for every pass (loads past the
-// pass's bytes repeat its last one, into the same LDS bytes).
-// ---------------------------------------------------------------------------
-constexpr int kRingSlots = 4;
-constexpr int kRingSlotMax = 32768;  // bytes of one pass's rows at most (a slot adds up to 1 KB of padding)
-constexpr int kProducerWaves = 4;
-constexpr int kConsumerWaves = 8;
-constexpr int kRingThreads = 64 * (kProducerWaves + kConsumerWaves);
-constexpr int kMaxRingRows = 64 * kConsumerWaves;  // rows per pass at most (one block per row)
-
-// vmcnt-only wait (expcnt and lgkmcnt left at their maxima).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
-// Workgroup barrier without the wait for loads in flight that __syncthreads
-// adds (the producers' loads must stay in flight across it).
-__device__ __forceinline__ void bare_barrier() { asm volatile("s_barrier" ::: "memory"); }
-
-__device__ __forceinline__ uint32_t uni32(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ __forceinline__ const uint8_t* uni_ptr(const uint8_t* p) {
-  const uint64_t v = (uint64_t)p;
-  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return (const uint8_t*)(lo | (hi << 32));
-}
-
-// Direct global -> LDS load: lane i's 16 bytes at sbase + voff land at M0 +
-// 16 i.  Inline asm, so the compiler neither tracks nor waits for it; the
-// producers' explicit vmcnt waits do.  The s_nop covers the M0 write.  The
-// rows are read once, so the load is marked non-temporal (nt): their lines
-// go first when the L2 evicts, and the partly written lines of the packed
-// codes (runs of a few rows that other workgroups complete) stay there to be
-// merged (8192 x 5120: 31.6 -> 28.6 us).
-__device__ __forceinline__ void dma16(uint32_t voff, const uint8_t* sbase, uint32_t lds) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" : : "v"(voff), "s"(sbase), "{m0}"(lds) : "memory");
-}
-
-// Square sums of the rows of the pass in the slot at `slot` (row r at r *
-// row_stride), one row per producer wavefront at a time, into the fp64
-// words at `sums`: four accumulators per lane over 16-byte reads, then a
-// fixed shuffle tree, so the result does not depend on timing (squares of
-// bf16 values are exact in fp64).
-__device__ __forceinline__ void ring_row_sums(uint32_t slot, int row_stride, int rpp, int K, int pw, int lane,
-                                              uint32_t sums) {
-  for (int r = pw; r < rpp; r += kProducerWaves) {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int c = lane; c < (K >> 3); c += 64) {
-      const u32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(
-          (uintptr_t)(slot + (uint32_t)r * (uint32_t)row_stride + (uint32_t)c * 16u));
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const double lo = (double)__uint_as_float(v[k] << 16), hi = (double)__uint_as_float(v[k] & 0xFFFF0000u);
-        acc[k] += lo * lo;
-        acc[k] += hi * hi;
-      }
-    }
-    double t = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-    if (lane == 0) *reinterpret_cast<__attribute__((address_space(3))) double*>((uintptr_t)(sums + 8u * r)) = t;
-  }
-}
-
-// kNorm: the RMSNorm in front.  The producers then also sum each pass's
-// squares one pass ahead (after the barrier at which pass k + 1 has landed,
-// into one of two sum buffers), so the consumers of pass k find its row
-// factors ready; this keeps one pass fewer in flight.
-template <int NPER, bool kNorm>
-__global__ __launch_bounds__(kRingThreads, 1) void quantize_ring_kernel(QuantArgs a, int rpp, int row_stride,
-                                                                       int slot_stride) {
-  extern __shared__ __attribute__((aligned(1024))) uint8_t ring[];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)ring;
-  // the norm's row square sums: two buffers of kMaxRingRows fp64 words after the slots
-  const uint32_t sums0 = lds0 + (uint32_t)kRingSlots * (uint32_t)slot_stride;
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int K = a.K;
-  const int nblk = K >> 5;
-  const int64_t passes = (a.rp + rpp - 1) / rpp;  // padding rows included
-
-  // this workgroup's passes: each XCD a contiguous range (the rows of a
-  // 32-row group share cache lines in the packed layout), its workgroups
-  // strided through it
+  // this workgroup's passes: workgroups are dealt to the 8 XCDs round-robin,
+  // each XCD takes a contiguous range of passes, so the rows of one 32-row
+  // group (which share cache lines in the packed layout) are written through
+  // one XCD's L2
+  const int64_t passes = (a.rp + RH - 1) / RH;
   int64_t q, q_end, stride;
   if (gridDim.x % 8 == 0) {
     const int x = blockIdx.x & 7;
@@ -539,313 +326,234 @@ __global__ __launch_bounds__(kRingThreads, 1) void quantize_ring_kernel(QuantArg
     stride = gridDim.x;
   }
   if (q >= q_end) return;  // uniform over the workgroup
-  const int64_t nk = (q_end - q + stride - 1) / stride;
 
-  if (wave >= kConsumerWaves) {
-    // producer: pass k goes to slot k % kRingSlots, row r of the pass at
-    // r * row_stride in the slot; wavefront pw issues the pass's 1 KB pieces
-    // pw, pw + 4, ... (a piece past the last repeats the last); passes past
-    // the workgroup's last repeat it
-    const int pw = wave - kConsumerWaves;
-    const int lane = tid & 63;
-    const int cpr = K >> 3;  // 16-byte chunks per row
-    // padded rows (row_stride > 2K, K a multiple of 512): whole 1 KB pieces
-    // per row; otherwise rows back to back, pieces across row ends
-    const bool padded = row_stride != 2 * K;
-    const int ipr = cpr >> 6;  // pieces per row when padded
-    const int nchunks = rpp * cpr;
-    const int ninstr = padded ? rpp * ipr : (nchunks + 63) >> 6;
-    auto issue = [&](int64_t k) {
-      const int64_t kk = k < nk ? k : nk - 1;
-      const int64_t r0 = (q + kk * stride) * rpp;
-      // rows past the input are read from its last row (their blocks
-      // quantise as padding and never use them)
-      const int64_t rb = r0 < a.rows ? r0 : a.rows - 1;
-      const uint8_t* base = uni_ptr(reinterpret_cast<const uint8_t*>(a.x + rb * a.ldx));
-      const uint32_t slot = lds0 + (uint32_t)(k % kRingSlots) * (uint32_t)slot_stride;
+  // A pass has four 16-byte chunks per thread.  Chunk j: up to four rows, the
+  // threads share a row's 4 / RH parts, so j alone gives row and part; above,
+  // RH / 4 rows per j, row_in the thread's.
+  constexpr int kParts = RH < 4 ? 4 / RH : 1, kRowsPer = RH < 4 ? 1 : RH / 4;
+  const int row_in = RH > 4 ? t / (K >> 3) : 0;
+  const int col = RH > 4 ? t - row_in * (K >> 3) : t;
+  u32x4 buf[4];
+  auto load = [&](int64_t p) {
 #pragma unroll
-      for (int j = 0; j < NPER; ++j) {
-        int i = pw + kProducerWaves * j;
-        i = i < ninstr ? i : ninstr - 1;
-        int rr, c;  // row within the pass, chunk within the row
-        uint32_t dst;
-        if (padded) {
-          rr = i / ipr;
-          const int ii = i - rr * ipr;
-          c = ii * 64 + lane;
-          dst = slot + (uint32_t)rr * (uint32_t)row_stride + (uint32_t)ii * 1024u;
-        } else {
-          int cc = i * 64 + lane;
-          cc = cc < nchunks ? cc : nchunks - 1;
-          rr = cc / cpr;
-          c = cc - rr * cpr;
-          dst = slot + (uint32_t)i * 1024u;
-        }
-        int64_t row = r0 + rr;
-        row = row < a.rows ? row : a.rows - 1;
-        const uint32_t voff = (uint32_t)((row - rb) * a.ldx * 2 + (int64_t)c * 16);
-        dma16(voff, base, uni32(dst));
-      }
-    };
-    for (int k = 0; k < kRingSlots - 1; ++k) issue(k);
-    if constexpr (kNorm) {
-      // the sums of pass 0 before the consumers start
-      wait_vmcnt<(kRingSlots - 2) * NPER>();
-      bare_barrier();
-      ring_row_sums(lds0, row_stride, rpp, K, pw, lane, sums0);
+    for (int j = 0; j < 4; ++j) {
+      int64_t row = p * RH + j / kParts * kRowsPer + row_in;
+      row = row < a.rows ? row : a.rows - 1;  // (padding rows quantise zeros)
+      const uint8_t* src = reinterpret_cast<const uint8_t*>(a.x + row * a.ldx + j % kParts * n_act * 8);
+      buf[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (uint32_t)col * 16u));
     }
-    for (int64_t k = 0; k < nk; ++k) {
-      // pass k landed (this wavefront's loads; the kRingSlots - 2 passes
-      // after it may still be in flight), then everyone's; with the norm
-      // pass k + 1 too, whose sums follow
-      wait_vmcnt<(kRingSlots - (kNorm ? 3 : 2)) * NPER>();
-      bare_barrier();
-      // the consumers are done with pass k - 1: refill its slot
-      issue(k + kRingSlots - 1);
-      if constexpr (kNorm)
-        if (k + 1 < nk)
-          ring_row_sums(lds0 + (uint32_t)((k + 1) % kRingSlots) * (uint32_t)slot_stride, row_stride, rpp, K, pw,
-                        lane, sums0 + (uint32_t)((k + 1) & 1) * 8u * kMaxRingRows);
-    }
-    wait_vmcnt<0>();  // no load may land after the workgroup's LDS is released
-    return;
-  }
+  };
+  load(q);
+  u32x4 gam[4 / RH + 1];
+  if constexpr (kNorm)
+#pragma unroll
+    for (int j = 0; j < 4 / RH; ++j) gam[j] = *reinterpret_cast<const u32x4*>(a.gamma + (int64_t)(j * n_act + t) * 8);
 
-  // consumer: thread t owns block t / rpp of pass-row t % rpp, so the
-  // lanes that store one block's codes hold consecutive rows, whose codes
-  // are consecutive in the packed layout (one contiguous run per block
-  // instead of one 16-byte piece per lane); with padded rows those lanes'
-  // gather reads fall on different banks
-  const int blk = tid / rpp;
-  const int prow = tid - blk * rpp;
-  const bool active = blk < nblk;
-  uint32_t addr[32];
-  const uint32_t base = lds0 + (uint32_t)prow * (uint32_t)row_stride;
+  // sigma of the thread's block; an out-of-range entry (a caller error) is
+  // clamped to stay inside the row
+  uint32_t sig[16];
 #pragma unroll
-  for (int qq = 0; qq < 8; ++qq) {
-    const int4 v = *reinterpret_cast<const int4*>(a.perm + (active ? blk : 0) * 32 + 4 * qq);
+  for (int k = 0; k < 8; ++k) {
+    const int4 v = *reinterpret_cast<const int4*>(a.perm + blk * 32 + 4 * k);
     const int p[4] = {v.x, v.y, v.z, v.w};
+    uint32_t o[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) addr[4 * qq + i] = base + 2u * (uint32_t)((unsigned)p[i] < (unsigned)K ? p[i] : 0);
+    for (int i = 0; i < 4; ++i) o[i] = 2u * (uint32_t)((unsigned)p[i] < (unsigned)K ? p[i] : 0);
+    sig[2 * k] = o[0] | (o[1] << 16);
+    sig[2 * k + 1] = o[2] | (o[3] << 16);
   }
-#pragma unroll
-  for (int i = 0; i < 32; ++i) asm volatile("" : "+v"(addr[i]));
-  // the norm weights of this thread's block, gathered by sigma, as bf16 pairs
-  uint32_t gpk[16];
   if constexpr (kNorm) {
+    // the weights in block order, gathered by sigma from a copy of gamma that
+    // takes the rows' place in LDS first (gathered from global memory, they
+    // would wait for sigma and then for themselves: 2 us)
 #pragma unroll
-    for (int qq = 0; qq < 8; ++qq) {
-      const int4 v = *reinterpret_cast<const int4*>(a.perm + (active ? blk : 0) * 32 + 4 * qq);
-      const int p[4] = {v.x, v.y, v.z, v.w};
-      uint32_t gg[4];
+    for (int j = 0; j < 4 / RH; ++j)
+      if (active) lds_store<u32x4>(lds0 + (uint32_t)(j * n_act + t) * 16u, gam[j]);
+    // sixteen wavefronts' sums; those of wavefronts that are not there stay zero
+    if (tid < kMaxThreads / 64 * RH) lds_store<double>(sums0 + (uint32_t)tid * 8u, 0.0);
+    __syncthreads();
+    if (active && prow == 0)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) gg[i] = a.gamma[(unsigned)p[i] < (unsigned)K ? p[i] : 0];
-      gpk[2 * qq] = gg[0] | (gg[1] << 16);
-      gpk[2 * qq + 1] = gg[2] | (gg[3] << 16);
-    }
-  } else {
+      for (int k = 0; k < 4; ++k) {
+        u32x4 g;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) gpk[i] = 0u;
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t s = sig[4 * k + i];
+          g[i] = lds_u16(add_word<0>(lds0, s)) | ((uint32_t)lds_u16(add_word<1>(lds0, s)) << 16);
+        }
+        lds_store<u32x4>(gam0 + (uint32_t)(k * nblk + blk) * 16u, g);
+      }
+    __syncthreads();
   }
-  const int bb = active ? blk : 0;
-  const int group = bb < a.nb[0] ? 0 : (bb < a.nb[0] + a.nb[1] ? 1 : 2);
-  const int b = bb - (group >= 1 ? a.nb[0] : 0) - (group >= 2 ? a.nb[1] : 0);
+  const int group = blk < a.nb[0] ? 0 : (blk < a.nb[0] + a.nb[1] ? 1 : 2);
+  const int b = blk - (group >= 1 ? a.nb[0] : 0) - (group >= 2 ? a.nb[1] : 0);  // block within its group
   const int gstep0 = (group >= 1 ? a.steps[0] : 0) + (group >= 2 ? a.steps[1] : 0);
-  const bool last = b == (group == 0 ? a.nb[0] : (group == 1 ? a.nb[1] : a.nb[2])) - 1;
-  if constexpr (kNorm) bare_barrier();  // the producers' barrier before pass 0's sums
-  for (int64_t k = 0; k < nk; ++k) {
-    bare_barrier();
-    const int64_t row = (q + k * stride) * rpp + prow;
+  const bool last = b == (group == 0 ? a.nb[0] : (group == 1 ? a.nb[1] : a.nb[2])) - 1;  // the group's last block
+
+  // where the thread's codes and scale byte of the rows 32 i + prow start
+  uint8_t* const dst = (group == 0 ? a.q[0] + code_offset<0>(b >> 2, a.rp, prow, b & 3)
+                                   : (group == 1 ? a.q[1] + code_offset<1>(b >> 2, a.rp, prow, b & 3)
+                                                 : a.q[2] + code_offset<2>(b >> 2, a.rp, prow, b & 3)));
+  uint8_t* const sdst = a.sc + ((gstep0 + (b >> 2)) * a.rp + prow) * kStepBlocks + (b & 3);
+
+  for (; q < q_end; q += stride) {
+    if constexpr (kNorm) {
+      double c[4] = {0.0, 0.0, 0.0, 0.0};  // of each chunk
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const double lo = (double)__uint_as_float(buf[j][k] << 16);
+          const double hi = (double)__uint_as_float(buf[j][k] & 0xFFFF0000u);
+          c[j] = fma(lo, lo, c[j]);
+          c[j] = fma(hi, hi, c[j]);
+        }
+      double sq[RH];
+      if constexpr (RH == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sq[i] = active ? c[i] : 0.0;
+      } else if constexpr (RH == 2) {
+        sq[0] = active ? c[0] + c[1] : 0.0;
+        sq[1] = active ? c[2] + c[3] : 0.0;
+      } else {
+        sq[0] = active ? (c[0] + c[1]) + (c[2] + c[3]) : 0.0;
+      }
+      const int lane = tid & 63;
+      const double s = wave_sums<RH>(sq, lane);
+      if (lane < RH) lds_store<double>(sums0 + (uint32_t)((tid >> 6) * RH + lane) * 8u, s);
+    }
+    if (active)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        lds_store<u32x4>(lds0 + (uint32_t)(j / kParts * kRowsPer + row_in) * row_stride +
+                             (uint32_t)(j % kParts * n_act + col) * 16u,
+                         buf[j]);
+    __syncthreads();
+    if (q + stride < q_end) load(q + stride);
     float rn = 0.0f;
     if constexpr (kNorm) {
-      // fp32(1 / sqrt(mean(x^2) + eps)) from the row's fp64 square sum
-      const double sq = *reinterpret_cast<const __attribute__((address_space(3))) double*>(
-          (uintptr_t)(sums0 + (uint32_t)(k & 1) * 8u * kMaxRingRows + 8u * (uint32_t)prow));
-      rn = (float)(1.0 / sqrt(sq / (double)K + (double)a.eps));
+      double p[8];
+#pragma unroll
+      for (int w = 0; w < 8; ++w) p[w] = lds_load<double>(sums0 + (uint32_t)(w * RH + prow) * 8u);
+      double s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      if (blockDim.x > 8 * 64) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) p[w] = lds_load<double>(sums0 + (uint32_t)((8 + w) * RH + prow) * 8u);
+        s += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      }
+      rn = rsqrt_f64(fma(s, a.inv_k, (double)a.eps));
     }
-    if (active && row < a.rp)
-      quantize_block<kNorm>(addr, (uint32_t)(k % kRingSlots) * (uint32_t)slot_stride, group, last, a, row, b,
-                            gstep0, gpk, rn);
-    // every read of this slot is done before the barrier that frees it
-    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
+    uint32_t base = lds0 + (uint32_t)prow * row_stride;
+    asm volatile("" : "+v"(base));  // (see add_word)
+    uint32_t d[16];
+    if constexpr (kNorm) {
+      // bf16(gamma * bf16(x * r)), fp32 products, each rounded to nearest even:
+      // eight channels at a time, the next eight's reads in flight (more would
+      // spill)
+      uint16_t e[2][8];
+      u32x4 gm[2];
+      auto read = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          e[k & 1][2 * i] = lds_u16(add_word<0>(base, sig[4 * k + i]));
+          e[k & 1][2 * i + 1] = lds_u16(add_word<1>(base, sig[4 * k + i]));
+        }
+        gm[k & 1] = lds_load<u32x4>(gam0 + (uint32_t)(k * nblk + blk) * 16u);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      read(0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (k < 3) read(k + 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t g = gm[k & 1][i];
+          const f32x2 x = {__uint_as_float((uint32_t)e[k & 1][2 * i] << 16) * rn,
+                           __uint_as_float((uint32_t)e[k & 1][2 * i + 1] << 16) * rn};
+          const uint32_t y = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+          const f32x2 z = {__uint_as_float(y << 16) * __uint_as_float(g << 16),
+                           __uint_as_float(y & 0xFFFF0000u) * __uint_as_float(g & 0xFFFF0000u)};
+          d[4 * k + i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(z, bf16x2));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {  // sixteen reads in flight at a time
+        uint16_t e[16];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          e[2 * i] = lds_u16(add_word<0>(base, sig[8 * h + i]));
+          e[2 * i + 1] = lds_u16(add_word<1>(base, sig[8 * h + i]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          u16x2 v;
+          v.x = e[2 * i];
+          v.y = e[2 * i + 1];
+          d[8 * h + i] = __builtin_bit_cast(uint32_t, v);
+        }
+      }
+    }
+    const int64_t row0 = q * RH;  // (a multiple of RH, so the pass lies in one row group)
+    if (active && row0 + prow < a.rp) encode_block(d, group, last, a, row0, prow, b, gstep0, dst, sdst);
+    __syncthreads();
   }
 }
 
-// Allow more than 64 KB of dynamic LDS (two 32 KB stages plus the dummy
-// slot and the row square sums, or one wide row and its weights).
-template <int kMaxThreads, bool kPipe, int kNorm>
-static hipError_t allow_lds(size_t bytes) {
-  static bool done = false;
-  if (done || bytes <= 65536) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(quantize_rows_kernel<kMaxThreads, kPipe, kNorm>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
-  if (e == hipSuccess) done = true;
-  return e;
-}
-
-// Workgroups of the pipelined kernel resident on the current device at once
-// (per-CU occupancy times CU count), cached per thread for the last shape.
-template <int kNorm>
-static hipError_t resident_workgroups(int T, size_t lds, int* cap) {
-  thread_local int last_dev = -1, last_T = 0, last_cap = 0;
-  thread_local size_t last_lds = 0;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev != last_dev || T != last_T || lds != last_lds) {
-    int per_cu = 0, cus = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, quantize_rows_kernel<512, true, kNorm>, T, lds);
-    if (e != hipSuccess) return e;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    last_dev = dev;
-    last_T = T;
-    last_lds = lds;
-    last_cap = (per_cu < 1 ? 1 : per_cu) * (cus < 1 ? 1 : cus);
-  }
-  *cap = last_cap;
-  return hipSuccess;
-}
-
-template <int kNorm>
-static hipError_t launch_pipelined(const QuantArgs& a, int rpp, int T, size_t lds, int gamma_off, hipStream_t stream) {
-  hipError_t e = allow_lds<512, true, kNorm>(lds);
-  if (e != hipSuccess) return e;
-  // one wave of workgroups: as many as the chip holds at once
-  int cap = 0;
-  e = resident_workgroups<kNorm>(T, lds, &cap);
-  if (e != hipSuccess) return e;
-  const int64_t passes = (a.rp + rpp - 1) / rpp;
-  const int64_t grid = passes < cap ? passes : cap;
-  hipLaunchKernelGGL((quantize_rows_kernel<512, true, kNorm>), dim3((unsigned)grid), dim3(T), lds, stream, a, rpp,
-                     gamma_off);
-  return hipGetLastError();
-}
-
-template <int NPER, bool kNorm>
-static hipError_t launch_ring_n(const QuantArgs& a, int rpp, int row_stride, int slot_stride, int grid,
-                                hipStream_t stream) {
+template <int RH, bool kNorm>
+static hipError_t launch_rows(const QuantArgs& a, hipStream_t stream) {
   static bool attr = false;
-  constexpr size_t kSumBytes = 2 * 8 * kMaxRingRows;
-  const size_t lds = (size_t)kRingSlots * slot_stride + (kNorm ? kSumBytes : 0);
+  constexpr int kLds = 160 * 1024;
   if (!attr) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(quantize_ring_kernel<NPER, kNorm>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kRingSlots * (kRingSlotMax + 1024) + kSumBytes);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(quantize_kernel<RH, kNorm>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (e != hipSuccess) return e;
     attr = true;
   }
-  hipLaunchKernelGGL((quantize_ring_kernel<NPER, kNorm>), dim3((unsigned)grid), dim3(kRingThreads), lds, stream, a,
-                     rpp, row_stride, slot_stride);
-  return hipGetLastError();
-}
-
-template <bool kNorm>
-static hipError_t launch_ring_norm(const QuantArgs& a, int nper, int rpp, int row_stride, int slot_stride, int grid,
-                                   hipStream_t stream) {
-  if (nper <= 1) return launch_ring_n<1, kNorm>(a, rpp, row_stride, slot_stride, grid, stream);
-  if (nper <= 2) return launch_ring_n<2, kNorm>(a, rpp, row_stride, slot_stride, grid, stream);
-  if (nper <= 4) return launch_ring_n<4, kNorm>(a, rpp, row_stride, slot_stride, grid, stream);
-  return launch_ring_n<8, kNorm>(a, rpp, row_stride, slot_stride, grid, stream);
-}
-
-// The ring kernel for K <= 8192 (passes of two or more rows), with or
-// without the norm; *used = false leaves the launch to the kernels below.
-static hipError_t launch_ring(const QuantArgs& a, hipStream_t stream, bool* used) {
-  *used = false;
-  const int K = a.K;
-  const int nblk = K >> 5;
-  if (nblk > 64 * kConsumerWaves || 2 * K > kRingSlotMax) return hipSuccess;
-  // rows per pass: as many as the consumer threads and one slot take
-  int rpp = 64 * kConsumerWaves / nblk;
-  if (rpp * 2 * K > kRingSlotMax) rpp = kRingSlotMax / (2 * K);
   int cus = 0;
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
-  // few rows (under eight passes per workgroup), plain quantiser: halve the
-  // pass while it keeps two or more rows, so that each workgroup's ring has
-  // more passes to overlap (2048 x 4096: 9.6 -> 8.8 us; 4096 x 4096, with
-  // the streamed loads: 15.5 -> 14.1 us; with the norm the producers' row
-  // sums then lose half their wavefronts, so not there)
-  while (a.norm == 0 && rpp >= 4 && (a.rp + rpp - 1) / rpp < 8 * (int64_t)cus) rpp /= 2;
-  // one row per pass (K > 8192): the pipelined kernel measured faster
-  // there (K = 14336: 35 us against 42 us for 4096 rows)
-  if (rpp < 2) return hipSuccess;
-  // per-lane load offsets are 32-bit, relative to the pass's first row
-  if ((int64_t)rpp * a.ldx * 2 + (int64_t)K * 2 >= ((int64_t)1 << 32)) return hipSuccess;
-  // rows padded by 16 bytes in LDS when they are whole 1 KB loads (K a
-  // multiple of 512) and the pass has several, so the gather reads of one
-  // block's rows fall on different banks
-  const bool padded = K % 512 == 0 && rpp > 1;
-  const int row_stride = padded ? 2 * K + 16 : 2 * K;
-  const int bytes = rpp * row_stride;
-  const int slot_stride = (bytes + 1023) / 1024 * 1024;  // the last 1 KB load may run past the pass's bytes
-  const int ninstr = padded ? rpp * (2 * K / 1024) : (bytes + 1023) / 1024;
-  const int nper = (ninstr + kProducerWaves - 1) / kProducerWaves;
-  const int64_t passes = (a.rp + rpp - 1) / rpp;
-  const int grid = (int)(passes < cus ? passes : cus);
-  *used = true;
-  if (a.norm != 0) return launch_ring_norm<true>(a, nper, rpp, row_stride, slot_stride, grid, stream);
-  return launch_ring_norm<false>(a, nper, rpp, row_stride, slot_stride, grid, stream);
+  const int waves = (RH * (a.K >> 5) + 63) / 64;
+  const size_t lds = (size_t)RH * (2 * a.K + 16) + (kNorm ? 2 * (size_t)a.K + 8 * (kMaxThreads / 64) * RH : 0);
+  if (64 * waves > kMaxThreads || lds > kLds) return hipErrorInvalidValue;  // cannot happen: see launch_quantize
+  // as many workgroups as the chip holds at once (16 wavefronts and 160 KB of
+  // LDS per CU), so that each keeps its sigma for all of its passes
+  int64_t per = 16 / waves;
+  if (per * lds > kLds) per = kLds / lds;
+  const int64_t passes = (a.rp + RH - 1) / RH, cap = per * cus;
+  hipLaunchKernelGGL((quantize_kernel<RH, kNorm>), dim3((unsigned)(passes < cap ? passes : cap)), dim3(64 * waves), lds,
+                     stream, a);
+  return hipGetLastError();
 }
 
-static hipError_t launch_quantize_rows(const QuantArgs& a, hipStream_t stream) {
-  const int K = a.K;
-  const int nblk = K >> 5;
-  const bool norm = a.norm != 0;
-  bool ring_used = false;
-  hipError_t re = launch_ring(a, stream, &ring_used);
-  if (re != hipSuccess || ring_used) return re;
-  // A row wider than one stage (K > 16384) is quantised without overlap, one
-  // row per workgroup of K/32 threads (up to 1024); with the norm its weights
-  // follow the row, the dummy slot and the (row, part) sums in LDS.
-  if (K * 2 > kStageOff) {
-    const int T = (nblk + 63) / 64 * 64;
-    const int gamma_off = K * 2 + 16 + 8 * 16;
-    if (norm) {
-      const size_t lds = (size_t)gamma_off + (size_t)K * 2;
-      hipError_t e = allow_lds<1024, false, 2>(lds);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((quantize_rows_kernel<1024, false, 2>), dim3((unsigned)a.rp), dim3(T), lds, stream, a, 1,
-                         gamma_off);
-    } else {
-      const size_t lds = (size_t)K * 2 + 16;
-      hipError_t e = allow_lds<1024, false, 0>(lds);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((quantize_rows_kernel<1024, false, 0>), dim3((unsigned)a.rp), dim3(T), lds, stream, a, 1, 0);
-    }
-    return hipGetLastError();
-  }
-  // rows per pass: the fewest idle lanes (ties: more rows) among launches of
-  // up to 512 threads, stopping at the first of at least 256 threads; a pass
-  // must fit one LDS stage
-  const int max_rpp = kStageOff / (K * 2);
-  int rpp = 1;
-  double best = 2.0;
-  for (int r = 1; r <= max_rpp && r * nblk <= 512; ++r) {
-    const int t = (r * nblk + 63) / 64 * 64;
-    const double idle = (double)(t - r * nblk) / t;
-    if (idle <= best) {
-      best = idle;
-      rpp = r;
-    }
-    if (t >= 256) break;
-  }
-  if (rpp > kMaxRowSlots) return hipErrorInvalidValue;  // cannot happen: rpp * nblk <= 512
-  const int T = (rpp * nblk + 63) / 64 * 64;
-  // two stages plus the 16-byte dummy slot (and the (row, part) square sums)
-  size_t lds = (size_t)kStageOff + (size_t)rpp * K * 2 + 16;
-  if (!norm) return launch_pipelined<0>(a, rpp, T, lds, 0, stream);
-  const int slots = rpp > T / 64 ? rpp : T / 64;  // max(rpp, waves)
-  lds += (size_t)slots * 8;
-  // the block-order weights fit the unused tail of stage 0
-  if ((rpp + 1) * K * 2 <= kStageOff) return launch_pipelined<2>(a, rpp, T, lds, rpp * K * 2, stream);
-  return launch_pipelined<1>(a, rpp, T, lds, 0, stream);
-}
-
+// Rows per pass.  As many as 1024 threads and a 64 KB of rows take (K <= 8192:
+// 4, <= 16384: 2) for the longest runs of codes per store; fewer rows give more
+// and smaller workgroups, which start and finish sooner, and win where there is
+// little to stream.  Measured (us, 1 / 2 / 4 rows per pass): 128 x 4096 3.6 / 3.7
+// / 4.3, 512 x 4096 4.7 / 4.5 / 5.0, 2048 x 4096 10.3 / 8.1 / 8.6, 4096 x 4096
+// 15.5 / 12.7 / 13.1, 14336 x 4096 42.6 / 35.1 / 33.0, 8192 x 5120 33 / 30.4 /
+// 25.0, with the norm 512 x 4096 7.6 / 6.5 / 8.0 and 8192 x 5120 43 / 48 / 41;
+// below 2048 channels four rows are never slower (1000 x 608: 4.0 / 3.9 / 3.6),
+// and up to 512 sixteen beat them without the norm (28672 x 512: 12.2 / 10.8).
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream) {
   if (a.rows == 0) return hipSuccess;
-  return launch_quantize_rows(a, stream);
+  const bool norm = a.norm != 0;
+  const int64_t n = a.rp * a.K;
+  int rh = a.K <= 8192 ? 4 : (a.K <= 16384 ? 2 : 1);
+  if (a.K >= 2048) {
+    if (n < (1 << 20)) rh = 1;
+    else if (n < (24 << 20) && rh > 2) rh = 2;
+  } else if (a.K <= 512 && !norm) {
+    rh = 16;
+  }
+  switch (rh) {
+    case 1: return norm ? launch_rows<1, true>(a, stream) : launch_rows<1, false>(a, stream);
+    case 2: return norm ? launch_rows<2, true>(a, stream) : launch_rows<2, false>(a, stream);
+    case 4: return norm ? launch_rows<4, true>(a, stream) : launch_rows<4, false>(a, stream);
+    default: return launch_rows<16, false>(a, stream);
+  }
 }
 
 }  // namespace mm

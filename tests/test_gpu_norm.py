@@ -95,6 +95,20 @@ def _gamma(K, seed):
 RAGGED = [(96, 160, 96), (352, 0, 0), (0, 352, 0), (0, 0, 352), (32, 32, 288)]
 
 
+@pytest.mark.parametrize("rows,K", [(70, 512), (35, 2016), (33, 2048), (520, 2080), (3, 8192), (140, 8192),
+                                    (3, 8224), (70, 15360), (33, 16416), (2, 32768)])
+def test_rows_per_pass(rows, K):
+    """1, 2 or 4 rows per pass by channels and values (the square sums of a
+    row come from all or some of the workgroup's wavefronts, up to sixteen)."""
+    p4, p6 = K // 2 // 32 * 32, K // 4 // 32 * 32
+    rng = np.random.default_rng(rows + K)
+    x = rng.standard_normal((rows, K), dtype=np.float32) * np.exp2(rng.integers(-6, 7, (rows, 1))).astype(np.float32)
+    x[:, rng.integers(K)] *= 100
+    g = (1.0 + 0.25 * rng.standard_normal(K)).astype(np.float32)
+    _check(W.f32_to_bf16_bits(x), W.f32_to_bf16_bits(g), 1e-5, rng.permutation(K).astype(np.int32),
+           (p4, p6, K - p4 - p6), ctx="rows per pass", ld_extra=8)
+
+
 @pytest.mark.parametrize("split", RAGGED)
 @pytest.mark.parametrize("rows", [1, 37])
 def test_ragged_shapes(split, rows):

@@ -46,6 +46,30 @@ RAGGED_SPLITS = [(96, 160, 96), (352, 0, 0), (0, 352, 0), (0, 0, 352), (32, 32, 
                  (256, 64, 32)]
 
 
+@pytest.mark.parametrize("rows,K", [(70, 512), (1, 32), (515, 64), (70, 544), (90, 2016), (33, 2048), (500, 2080),
+                                    (3, 8192), (140, 8192), (3010, 8192), (3, 8224), (65, 16384), (33, 16416),
+                                    (2, 32768)])
+def test_rows_per_pass(rows, K):
+    """The sizes at which the kernel changes its rows per pass (16 up to 512
+    channels, 4 below 2048, then 1, 2 or 4 by the number of values, at most 2
+    above 8192 and 1 above 16384 channels), with last passes of padding rows
+    only.  Large inputs are compared on sampled rows."""
+    p4, p6 = K // 2 // 32 * 32, K // 4 // 32 * 32
+    split = (p4, p6, K - p4 - p6)
+    note(f"rows per pass rows={rows} K={K}")
+    rng = np.random.default_rng(rows + K)
+    x = rng.standard_normal((rows, K), dtype=np.float32)
+    x[:, rng.integers(K)] *= 300
+    bits = W.f32_to_bf16_bits(x)
+    perm = rng.permutation(K).astype(np.int32)
+    got = _run(bits, perm, split, ld_extra=8)
+    if rows * K < 1 << 21:
+        assert_codes_equal(got, O.quantize_mixed(bits, perm, split), ctx=f"{rows}x{K}")
+    else:
+        some = np.unique(np.concatenate([np.arange(9), rows - 1 - np.arange(9), rng.integers(0, rows, 40)]))
+        assert_codes_equal(got, O.quantize_mixed(bits[some], perm, split), rows=some, ctx=f"{rows}x{K}")
+
+
 @pytest.mark.parametrize("split", RAGGED_SPLITS)
 @pytest.mark.parametrize("rows", [1, 37])
 def test_ragged_shapes(split, rows):
