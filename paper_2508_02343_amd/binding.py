@@ -8,7 +8,9 @@ is missing the import of this module fails loudly; there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
+import struct
 from dataclasses import dataclass
 
 import torch
@@ -88,6 +90,26 @@ def _load(path: str = LIB_PATH) -> ctypes.CDLL:
 
 lib = _load()
 
+# The launching calls once more, with descriptors passed as packed bytes (an
+# mm_mx_tensor, field by field) instead of ctypes structures: at decode sizes a
+# kernel takes 4 us, and filling a structure took 1 us of each call's time.
+_DESC = struct.Struct("@qqiiiiiPPPP")
+assert _DESC.size == ctypes.sizeof(MMTensor)
+
+
+def _load_packed(path: str = LIB_PATH) -> ctypes.CDLL:
+    fast = ctypes.CDLL(path)
+    P, I64, D = ctypes.c_void_p, ctypes.c_int64, ctypes.c_char_p
+    fast.mm_quantize_act.argtypes = fast.mm_quantize_weight.argtypes = [P, I64, P, D, P]
+    fast.mm_rmsnorm_quantize_act.argtypes = [P, I64, P, ctypes.c_float, P, D, P]
+    fast.mm_gemm.argtypes = [D, D, P, I64, P]
+    for f in (fast.mm_quantize_act, fast.mm_quantize_weight, fast.mm_gemm, fast.mm_rmsnorm_quantize_act):
+        f.restype = ctypes.c_int
+    return fast
+
+
+_fast = _load_packed()
+
 
 class MMError(RuntimeError):
     def __init__(self, status: int, message: str):
@@ -111,10 +133,25 @@ def layout_sizes(rows: int, K: int, split) -> dict:
     return {"q4": sz.q4, "q6": sz.q6, "q8": sz.q8, "sc": sz.sc}
 
 
+@functools.lru_cache(maxsize=1024)
+def _buffer_sizes(rows: int, K: int, split: tuple) -> tuple:
+    """layout_sizes as (q4, q6, q8, sc), remembered by value."""
+    sz = layout_sizes(rows, K, split)
+    return sz["q4"], sz["q6"], sz["q8"], sz["sc"]
+
+
 def _stream_ptr(stream) -> ctypes.c_void_p:
     if stream is None:
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream)
+
+
+def _stream_int(stream) -> int:
+    """The hipStream_t to launch on, without making a Stream object for the
+    current one (3 us)."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 @dataclass
@@ -134,15 +171,14 @@ class MXTensor:
 
     @classmethod
     def empty(cls, rows: int, K: int, split, device="cuda", formats=DEFAULT_FORMATS) -> "MXTensor":
-        split = tuple(int(p) for p in split)
-        sz = layout_sizes(rows, K, split)
+        split = tuple(map(int, split))
 
         def buf(nbytes):
             if nbytes == 0:
                 return None
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
-        return cls(rows, K, split, buf(sz["q4"]), buf(sz["q6"]), buf(sz["q8"]), buf(sz["sc"]), tuple(formats))
+        return cls(rows, K, split, *map(buf, _buffer_sizes(rows, K, split)), tuple(formats))
 
     def descriptor(self) -> MMTensor:
         d = MMTensor()
@@ -155,6 +191,18 @@ class MXTensor:
             setattr(d, name, t.data_ptr() if t is not None else None)
         return d
 
+    def _packed(self) -> bytes:
+        """descriptor() as the bytes of an mm_mx_tensor."""
+        split = self.split
+        if len(split) != 3:
+            split = MMSplit(*split)
+            split = (split.p4, split.p6, split.p8)
+        q4, q6, q8 = self.q4, self.q6, self.q8
+        return _DESC.pack(self.rows, self.K, *split, FP6_FORMATS.get(self.formats[0], -1),
+                          FP8_FORMATS.get(self.formats[1], -1), 0 if q4 is None else q4.data_ptr(),
+                          0 if q6 is None else q6.data_ptr(), 0 if q8 is None else q8.data_ptr(),
+                          0 if self.sc is None else self.sc.data_ptr())
+
     def raw_host(self) -> dict:
         """The four buffers' bytes as numpy arrays (empty for an absent group)."""
         import numpy as np
@@ -166,33 +214,34 @@ class MXTensor:
 def _check_mx(t: MXTensor, rows: int, K: int, split, device, name: str) -> None:
     """An MXTensor whose buffers hold the packed layout of (rows, K, split)
     on `device` (the library reads and writes exactly those bytes)."""
-    if t.rows != rows or t.K != K or tuple(int(p) for p in t.split) != tuple(int(p) for p in split):
+    if t.rows != rows or t.K != K or (t.split != split and tuple(map(int, t.split)) != tuple(map(int, split))):
         raise ValueError(f"{name} is [{t.rows}, {t.K}] split {tuple(t.split)}, expected [{rows}, {K}] split "
                          f"{tuple(split)}")
-    sz = layout_sizes(rows, K, split)
-    for b in ("q4", "q6", "q8", "sc"):
-        buf = getattr(t, b)
-        n = 0 if buf is None else buf.numel() * buf.element_size()
-        if n < sz[b]:
-            raise ValueError(f"{name}.{b} holds {n} bytes, the layout needs {sz[b]}")
-        if buf is not None and (buf.device != device or not buf.is_contiguous()):
+    index = -1 if device.type == "cpu" else device.index  # (comparing devices costs four times as much)
+    bufs = (t.q4, t.q6, t.q8, t.sc)
+    for buf, need in zip(bufs, _buffer_sizes(rows, K, split if type(split) is tuple else tuple(map(int, split)))):
+        if (need > 0) if buf is None else (buf.nbytes < need or buf.get_device() != index or not buf.is_contiguous()):
+            b = ("q4", "q6", "q8", "sc")[[x is buf for x in bufs].index(True)]
+            n = 0 if buf is None else buf.nbytes
+            if n < need:
+                raise ValueError(f"{name}.{b} holds {n} bytes, the layout needs {need}")
             raise ValueError(f"{name}.{b} must be contiguous and on {device}")
 
 
-def _quantize(fn, x: torch.Tensor, perm: torch.Tensor, split, out: MXTensor | None, stream, formats) -> MXTensor:
+def _quantize(fn, x: torch.Tensor, perm: torch.Tensor, split, out: MXTensor | None, stream, formats,
+              norm: tuple = ()) -> MXTensor:
     if x.dtype != torch.bfloat16 or x.dim() != 2 or x.stride(1) != 1 or not x.is_cuda:
         raise ValueError("x must be a 2-D row-major bfloat16 device tensor")
     rows, K = x.shape
-    if perm.dtype != torch.int32 or not perm.is_contiguous() or perm.numel() != K or perm.device != x.device:
+    device = x.device
+    if perm.dtype != torch.int32 or not perm.is_contiguous() or perm.numel() != K or perm.device != device:
         raise ValueError("perm must be a contiguous int32 tensor of K elements on x's device")
-    split = tuple(int(p) for p in split)
+    split = tuple(map(int, split))
     if out is None:
-        out = MXTensor.empty(rows, K, split, device=x.device, formats=formats)
+        out = MXTensor.empty(rows, K, split, device=device, formats=formats)
     else:
-        _check_mx(out, rows, K, split, x.device, "out")
-    d = out.descriptor()
-    _check(fn(ctypes.c_void_p(x.data_ptr()), x.stride(0), ctypes.c_void_p(perm.data_ptr()), ctypes.byref(d),
-              _stream_ptr(stream)))
+        _check_mx(out, rows, K, split, device, "out")
+    _check(fn(x.data_ptr(), x.stride(0), *norm, perm.data_ptr(), out._packed(), _stream_int(stream)))
     return out
 
 
@@ -200,7 +249,7 @@ def quantize_act(x: torch.Tensor, perm: torch.Tensor, split, out: MXTensor | Non
                  formats=DEFAULT_FORMATS) -> MXTensor:
     """mm_quantize_act: fused reorder-and-quantize of bf16 activations
     (formats: of the 6-bit and 8-bit groups, used when out is None)."""
-    return _quantize(lib.mm_quantize_act, x, perm, split, out, stream, formats)
+    return _quantize(_fast.mm_quantize_act, x, perm, split, out, stream, formats)
 
 
 def rmsnorm_quantize_act(x: torch.Tensor, gamma: torch.Tensor, eps: float, perm: torch.Tensor, split,
@@ -209,35 +258,30 @@ def rmsnorm_quantize_act(x: torch.Tensor, gamma: torch.Tensor, eps: float, perm:
     aligned, eps) fused with the reorder-and-quantize of bf16 activations."""
     if gamma.dtype != torch.bfloat16 or gamma.dim() != 1 or not gamma.is_contiguous() or gamma.numel() != x.shape[-1]:
         raise ValueError("gamma must be a contiguous bfloat16 tensor [K]")
-    g = ctypes.c_void_p(gamma.data_ptr())
-
-    def fn(xp, ld, pp, d, st):
-        return lib.mm_rmsnorm_quantize_act(xp, ld, g, ctypes.c_float(eps), pp, d, st)
-
-    return _quantize(fn, x, perm, split, out, stream, formats)
+    return _quantize(_fast.mm_rmsnorm_quantize_act, x, perm, split, out, stream, formats, (gamma.data_ptr(), eps))
 
 
 def quantize_weight(w: torch.Tensor, perm: torch.Tensor, split, out: MXTensor | None = None,
                     stream=None, formats=DEFAULT_FORMATS) -> MXTensor:
     """mm_quantize_weight: offline reorder-and-quantize of a bf16 weight [N, K]
     (formats as for quantize_act)."""
-    return _quantize(lib.mm_quantize_weight, w, perm, split, out, stream, formats)
+    return _quantize(_fast.mm_quantize_weight, w, perm, split, out, stream, formats)
 
 
 def gemm(a: MXTensor, w: MXTensor, y: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """mm_gemm: Y[M, N] = A W^T in bf16 (one fp32 accumulator over all groups)."""
-    dev = a.sc.device
-    _check_mx(a, a.rows, a.K, a.split, dev, "a")
-    _check_mx(w, w.rows, w.K, w.split, dev, "w")
+    device = a.sc.device
+    _check_mx(a, a.rows, a.K, a.split, device, "a")
+    _check_mx(w, w.rows, w.K, w.split, device, "w")
+    M, N = a.rows, w.rows
     if y is None:
-        ldy = _round16(w.rows) if w.rows % 8 else w.rows
-        y = torch.empty((a.rows, ldy), dtype=torch.bfloat16, device=dev)[:, : w.rows]
-    elif (y.dtype != torch.bfloat16 or y.dim() != 2 or tuple(y.shape) != (a.rows, w.rows) or y.stride(1) != 1
-          or y.device != dev):
-        raise ValueError(f"y must be a bfloat16 [{a.rows}, {w.rows}] tensor with unit column stride on {dev}")
-    da, dw = a.descriptor(), w.descriptor()
-    _check(lib.mm_gemm(ctypes.byref(da), ctypes.byref(dw), ctypes.c_void_p(y.data_ptr()), y.stride(0),
-                       _stream_ptr(stream)))
+        y = torch.empty((M, _round16(N) if N % 8 else N), dtype=torch.bfloat16, device=device)
+        if N % 8:
+            y = y[:, :N]
+    elif (y.dtype != torch.bfloat16 or y.dim() != 2 or tuple(y.shape) != (M, N) or y.stride(1) != 1
+          or y.device != device):
+        raise ValueError(f"y must be a bfloat16 [{M}, {N}] tensor with unit column stride on {device}")
+    _check(_fast.mm_gemm(a._packed(), w._packed(), y.data_ptr(), y.stride(0), _stream_int(stream)))
     return y
 
 
