@@ -245,7 +245,7 @@ mm_status mm_calibrate_workspace_size(int64_t rows, int64_t K, int64_t* bytes);
  *   perm_out   device, int32 [K], 16-byte aligned: sigma.
  *   split_out  device, int32 [3]: (p4, p6, p8); (-1, -1, -1) when X holds an
  *              Inf or NaN, and then perm_out is the identity.
- * Like every call it only enqueues work on `stream` (four launches); read
+ * Like every call it only enqueues work on `stream` (three or four launches); read
  * split_out after the stream has reached it.  rows >= 1, K a positive
  * multiple of 32, at most 32768.  Errors: MM_ERR_NULL, MM_ERR_SHAPE,
  * MM_ERR_ALIGN, MM_ERR_FORMAT, MM_ERR_WORKSPACE, MM_ERR_DEVICE.

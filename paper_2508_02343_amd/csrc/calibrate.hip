@@ -9,12 +9,15 @@
 // rounded down to a multiple of 32, so channels only ever move to a wider
 // group.
 //
-// Four stream-ordered launches, deterministic for a given (L, K):
+// Stream-ordered launches, deterministic for a given (L, K):
 //   1. column sums: each workgroup adds |x| in fp64 over one 512-channel tile
 //      and one fixed chunk of rows (HBM-bound, 2 bytes read per element) and
 //      writes its partial sums and its largest |x|.  About one workgroup per
 //      CU streams best: more concurrent row streams lose DRAM locality;
-//   2. means: each channel adds its chunk partials in a fixed order, / L;
+//   2. means: each channel adds its chunk partials in a fixed order, / L.  Up
+//      to kFuseK channels the rank workgroups do this for the channels that
+//      they compare, again in each workgroup, which is less than a launch of
+//      its own and the wait for it;
 //   3. rank: workgroup (jb, sl) compares 256 channels with a 256-channel
 //      slice of the means and stores, per channel, how many of them sort
 //      before it under the strict order (mean, index); the workgroups of
@@ -22,6 +25,11 @@
 //      their channels' groups;
 //   4. place: rank[j] = the sum of j's slice counts, sigma[rank[j]] = j, and
 //      workgroup 0 sums the group counts into the split.
+// Measured, whole call (us, separate means -> fused): 32768 x 4096 59.2 -> 54.7
+// (column sums 41.5), 2048 x 4096 22.2 -> 18.8, 300 x 1024 21.8 -> 16.4, 32768 x
+// 5120 73.3 -> 71.6, but 16384 x 14336 106 -> 120 and 2000 x 32768 114 -> 195
+// (every mean formed K / 256 times), so above kFuseK channels the means stay
+// a launch of their own.
 // No atomics: every result is written by exactly one thread.
 #include <mutex>
 
@@ -41,8 +49,9 @@ namespace {
 constexpr int kSumWaves = 4;               // waves per column-sum workgroup
 constexpr int kLaneCols = 8;               // channels per lane (one 16-byte load)
 constexpr int kTileCols = 64 * kLaneCols;  // channels per column-sum workgroup
-constexpr int kMeanWaves = 16;             // waves per mean workgroup (one chunk subset each)
+constexpr int kMeanChains = 16;            // partial sums of a mean (one chunk subset each)
 constexpr int kRankThreads = 256;          // channels per rank workgroup
+constexpr int kFuseK = 8192;               // channels up to which the rank kernel forms the means
 constexpr int kRankSlice = kCalibSlice;    // means compared per rank workgroup
 constexpr uint32_t kF32Inf = 0x7F800000u;  // |x| fp32 patterns at or above this are Inf or NaN
 
@@ -83,14 +92,35 @@ __device__ __forceinline__ int wave_sum(int v) {
 }
 
 // Largest |x| of the whole input (fp32 bit pattern), from the column-sum
-// workgroups' maxima; every thread of a kRankThreads workgroup gets it.
+// workgroups' maxima; every thread of the workgroup gets it, the first
+// kRankThreads look for it.
 __device__ uint32_t input_amax(const CalibArgs& a, uint32_t* lds4) {
   uint32_t m = 0u;
-  for (int i = threadIdx.x; i < a.nmax; i += kRankThreads) m = max(m, a.wgmax[i]);
+  if (threadIdx.x < kRankThreads)
+    for (int i = threadIdx.x; i < a.nmax; i += kRankThreads) m = max(m, a.wgmax[i]);
   m = wave_max(m);
-  if ((threadIdx.x & 63) == 0) lds4[threadIdx.x >> 6] = m;
+  if (threadIdx.x < kRankThreads && (threadIdx.x & 63) == 0) lds4[threadIdx.x >> 6] = m;
   __syncthreads();
   return max(max(lds4[0], lds4[1]), max(lds4[2], lds4[3]));
+}
+
+// Mean |x| of channel j: chain w adds the partials of chunks w, w + 16, ... in
+// order, the chains are added in order.
+__device__ __forceinline__ double channel_mean(const CalibArgs& a, int j) {
+  const double* p = a.partial + j;
+  double s[kMeanChains];
+#pragma unroll
+  for (int w = 0; w < kMeanChains; ++w) s[w] = w < a.nchunks ? p[(int64_t)w * a.K] : 0.0;
+  for (int c0 = kMeanChains; c0 < a.nchunks; c0 += kMeanChains) {
+    double v[kMeanChains];
+#pragma unroll
+    for (int w = 0; w < kMeanChains; ++w) v[w] = c0 + w < a.nchunks ? p[(int64_t)(c0 + w) * a.K] : 0.0;
+#pragma unroll
+    for (int w = 0; w < kMeanChains; ++w) s[w] += v[w];
+  }
+#pragma unroll
+  for (int w = 1; w < kMeanChains; ++w) s[0] += s[w];
+  return s[0] / (double)a.rows;
 }
 
 // How many of the n means in `tile` (channels base .. base+n-1, n a multiple
@@ -156,35 +186,51 @@ __global__ __launch_bounds__(64 * kSumWaves) void colsum_kernel(CalibArgs a) {
   for (int i = 0; i < kLaneCols / 2; ++i) out[i] = make_double2(s[2 * i], s[2 * i + 1]);
 }
 
-__global__ __launch_bounds__(64 * kMeanWaves) void mean_kernel(CalibArgs a) {
-  __shared__ double red[kMeanWaves][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + lane;
-  double s = 0.0;
-  if (j < a.K)
-    for (int c = wave; c < a.nchunks; c += kMeanWaves) s += a.partial[(int64_t)c * a.K + j];
-  red[wave][lane] = s;
-  __syncthreads();
-  if (wave != 0 || j >= a.K) return;
-  for (int w = 1; w < kMeanWaves; ++w) s += red[w][lane];
-  a.mean[j] = s / (double)a.rows;
+__global__ __launch_bounds__(kRankThreads) void mean_kernel(CalibArgs a) {
+  const int j = blockIdx.x * kRankThreads + threadIdx.x;
+  if (j < a.K) a.mean[j] = channel_mean(a, j);
 }
 
-__global__ __launch_bounds__(kRankThreads) void rank_kernel(CalibArgs a) {
+// kParts: threads per channel, each comparing with its part of the slice (the
+// chain of comparisons sets the kernel's length while there are few
+// workgroups).  kFuse: form the means here.
+template <int kParts, bool kFuse>
+__global__ __launch_bounds__(kRankThreads * kParts) void rank_kernel(CalibArgs a) {
+  static_assert(!kFuse || kParts >= 2, "part 0 forms the channels' means, part 1 the slice's");
   __shared__ __align__(16) double tile[kRankSlice];
+  __shared__ double mean[kFuse ? kRankThreads : 1];
+  __shared__ int part_cnt[kParts][kRankThreads];
   __shared__ uint32_t lds4[4];
   __shared__ int c4[4], c6[4];
-  const int jb = blockIdx.x * kRankThreads, j = jb + threadIdx.x;
+  const int tl = threadIdx.x % kRankThreads, part = threadIdx.x / kRankThreads;
+  const int jb = blockIdx.x * kRankThreads, j = jb + tl;
   const int base = blockIdx.y * kRankSlice;
   const int n = min(kRankSlice, a.K - base);
-  const double mj = j < a.K ? a.mean[j] : 0.0;
-  for (int i = threadIdx.x; i < n; i += kRankThreads) tile[i] = a.mean[base + i];
-  __syncthreads();
+  double mj;
+  if constexpr (kFuse) {
+    if (part == 0) mean[tl] = j < a.K ? channel_mean(a, j) : 0.0;
+    else if (part == 1 && tl < n) tile[tl] = channel_mean(a, base + tl);
+    __syncthreads();
+    mj = mean[tl];
+  } else {
+    mj = j < a.K ? a.mean[j] : 0.0;
+    if (part == 0 && tl < n) tile[tl] = a.mean[base + tl];
+    __syncthreads();
+  }
+  // this part's share of the slice, whole 32s (n is a multiple of 32)
+  const int per = (n / 32 + kParts - 1) / kParts * 32;
+  const int lo = min(n, part * per), m = min(n, lo + per) - lo;
   int cnt;
-  if (jb + kRankThreads <= base) cnt = count_before<0>(tile, n, mj, 0);  // uniform per workgroup
-  else if (jb >= base + n) cnt = count_before<1>(tile, n, mj, 0);
-  else cnt = count_before<2>(tile, n, mj, j - base);
-  if (j < a.K) a.slice_counts[(int64_t)blockIdx.y * a.K + j] = cnt;
+  if (jb + kRankThreads <= base) cnt = count_before<0>(tile + lo, m, mj, 0);  // uniform per workgroup
+  else if (jb >= base + n) cnt = count_before<1>(tile + lo, m, mj, 0);
+  else cnt = count_before<2>(tile + lo, m, mj, j - base - lo);
+  if constexpr (kParts > 1) {
+    part_cnt[part][tl] = cnt;
+    __syncthreads();
+#pragma unroll
+    for (int p = 1; p < kParts; ++p) cnt += part_cnt[p][tl];  // (of use in part 0)
+  }
+  if (part == 0 && j < a.K) a.slice_counts[(int64_t)blockIdx.y * a.K + j] = cnt;
   if (blockIdx.y != 0) return;
   // group counts of this workgroup's channels (slice 0 only: once per channel)
   const uint32_t amax = input_amax(a, lds4);
@@ -196,7 +242,7 @@ __global__ __launch_bounds__(kRankThreads) void rank_kernel(CalibArgs a) {
   const bool in4 = j < a.K && mj <= t4;
   const bool in6 = j < a.K && !in4 && mj <= t6;
   const int n4 = wave_sum(in4), n6 = wave_sum(in6);
-  if ((threadIdx.x & 63) == 0) {
+  if (part == 0 && (threadIdx.x & 63) == 0) {
     c4[threadIdx.x >> 6] = n4;
     c6[threadIdx.x >> 6] = n6;
   }
@@ -259,9 +305,13 @@ hipError_t calibrate_scratch(void** ptr) {
 hipError_t launch_calibrate(const CalibArgs& a, hipStream_t stream) {
   const int tiles = (a.K + kTileCols - 1) / kTileCols;
   hipLaunchKernelGGL(colsum_kernel, dim3(tiles, a.nchunks), dim3(64 * kSumWaves), 0, stream, a);
-  hipLaunchKernelGGL(mean_kernel, dim3((a.K + 63) / 64), dim3(64 * kMeanWaves), 0, stream, a);
-  hipLaunchKernelGGL(rank_kernel, dim3((a.K + kRankThreads - 1) / kRankThreads, (a.K + kRankSlice - 1) / kRankSlice),
-                     dim3(kRankThreads), 0, stream, a);
+  const dim3 ranks((a.K + kRankThreads - 1) / kRankThreads, (a.K + kRankSlice - 1) / kRankSlice);
+  if (a.K <= kFuseK) {
+    hipLaunchKernelGGL((rank_kernel<4, true>), ranks, dim3(kRankThreads * 4), 0, stream, a);
+  } else {
+    hipLaunchKernelGGL(mean_kernel, dim3((a.K + kRankThreads - 1) / kRankThreads), dim3(kRankThreads), 0, stream, a);
+    hipLaunchKernelGGL((rank_kernel<1, false>), ranks, dim3(kRankThreads), 0, stream, a);
+  }
   hipLaunchKernelGGL(place_kernel, dim3((a.K + kRankThreads - 1) / kRankThreads), dim3(kRankThreads), 0, stream, a);
   return hipGetLastError();
 }

@@ -86,6 +86,17 @@ def test_full_calibration_sets():
         _check(W.calibration_bits(L, K, seed), ctx=f"full{seed}")
 
 
+@pytest.mark.parametrize("L,K", [(5, 256), (1100, 288), (70, 8160), (2100, 8192), (70, 8224)])
+def test_means_in_the_rank_kernel(L, K):
+    """Up to 8192 channels the rank kernel forms the means itself (1 to 128 row
+    chunks, a last slice of 32 channels), above that they are a launch of their
+    own; columns that are equal in pairs half the width apart must keep their
+    order whichever workgroups compare them."""
+    bits = W.calibration_bits(L, K, L + K)
+    bits[:, K // 2:K // 2 + 40] = bits[:, :40]
+    _check(bits, ctx="rank means")
+
+
 def test_strided_rows():
     _check(W.calibration_bits(100, 1024, 20), ctx="ld+40", ld_extra=40)
 
