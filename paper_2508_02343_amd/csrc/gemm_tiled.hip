@@ -54,8 +54,6 @@ namespace tiled {
 constexpr int kLdsBytes = 160 * 1024;
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kCodeLoads = 8;  // code loads per wavefront and stage
-constexpr int kLoads = kCodeLoads + 1;  // + the scale load
 
 // A stage of group G: E2M1 one layout step (two 64-channel slices), E3M2 and
 // E4M3 half a step (one slice).
@@ -78,6 +76,10 @@ struct Tile {
   // its K loop starts after four stages instead of six and it measured 2-4 %
   // faster (2048 x 4096 x 4096: 30.8 -> 30.1 us)
   static constexpr int kSlots = 4;
+  // a wavefront's loads of a stage: a quarter of each operand's codes, and a
+  // scale load
+  static constexpr int kLoadsW = BN / 64, kLoadsX = BM / 64;
+  static constexpr int kCodeLoads = kLoadsW + kLoadsX, kLoads = kCodeLoads + 1;
   static_assert(BN == 256 && (BM == 256 || BM == 128), "tile shapes");
   static_assert(kSlots * kSlotBytes <= kLdsBytes, "the ring fits LDS");
   static_assert((kSlots - 1) * kLoads < 64, "vmcnt range");
@@ -155,60 +157,71 @@ __device__ __forceinline__ V opaque_s(V v) {
 // DMA cursor: where the next stage to issue comes from and goes to.
 // ---------------------------------------------------------------------------
 
+// One operand's codes: at the tile's first row per group, bytes between
+// layout steps per group (padded rows x step row bytes), the last row group
+// (relative to the tile) with rows, and the LDS offset of its part of a slot
+// (2 KB and 1.5 KB row-group shares).
+struct DmaCodes {
+  const uint8_t *code0, *code1, *code2;
+  int64_t rstride0, rstride1, rstride2;
+  int last;
+  uint32_t lds, lds6;
+};
+
 // Per-tile constants of this wavefront's loads.
 struct DmaConst {
-  const uint8_t* code0;    // this wavefront's operand codes at the tile's first row, per group
-  const uint8_t* code1;
-  const uint8_t* code2;
-  int64_t rstride0;        // bytes between layout steps of a group (padded rows x step row bytes)
-  int64_t rstride1;
-  int64_t rstride2;
+  DmaCodes w, x;
   const uint8_t* sc;       // this wavefront's operand scales at the tile's first row, layout step 0
   int64_t sstride;         // bytes between layout steps of the scales
   uint32_t soff;           // this lane's byte offset for the scale load
   uint32_t sdst;           // LDS offset of this wavefront's scale words in a slot
   uint64_t smask;          // lanes that take part in the scale load
-  int last;                // last row group (relative to the tile) with rows, of this wavefront's operand
-  int rows_op;             // tile rows of this wavefront's operand (BN or BM)
-  int op;                  // 0: weight rows, 1: activation rows
-  int half;                // which half of the operand's share this wavefront loads
-  uint32_t op_lds;         // LDS offset of the operand's codes in a slot (2 KB row-group shares)
-  uint32_t op_lds6;        // the same for 1.5 KB shares
+  int wave;
 };
 
 // The state that advances stage by stage.
+template <int NW, int NX>
 struct DmaCursor {
-  const uint8_t* bc;  // code base of the next stage to issue
-  const uint8_t* bs;  // scale base of the next stage to issue
-  int q;              // its stage index (it stays on the last stage: later issues repeat it)
-  int g;              // its group
-  int u;              // its half of the layout step (E3M2 / E4M3)
+  const uint8_t *bw, *bx;  // code bases of the next stage to issue
+  const uint8_t* bs;       // scale base of the next stage to issue
+  int u;                   // its half of the layout step (E3M2 / E4M3)
   // the step to the next stage inside a segment (see run_group): code and
   // scale base increments when u is 0 / 1, and whether u alternates
-  int64_t inc0, inc1, sinc0, sinc1;
+  int64_t winc0, winc1, xinc0, xinc1, sinc0, sinc1;
   int flip;
-  uint32_t doff[kCodeLoads];  // this lane's global byte offset for each code load of group g
-  uint32_t mo[kCodeLoads];    // LDS offset (in a slot) of each code load of group g
+  uint32_t wdoff[NW], xdoff[NX];  // this lane's global byte offset for each code load of group g
+  uint32_t wmo[NW], xmo[NX];      // LDS offset (in a slot) of each code load of group g
 };
 
-// Per-lane offsets of group G's code loads for this wavefront.
-template <int G>
-__device__ __forceinline__ void group_offsets(const DmaConst& k, DmaCursor& cur, int lane) {
+// Per-lane offsets of a wavefront's N loads of one operand's share of a group
+// G stage (`rows` tile rows): its quarter, completed by repeating pieces (into
+// the same LDS bytes with the same data) where the share has fewer.
+template <int G, int N>
+__device__ __forceinline__ void operand_offsets(const DmaCodes& k, int rows, int wave, uint32_t (&doff)[N],
+                                                uint32_t (&mo)[N], int lane) {
   constexpr int GB = stage_grp_bytes(G);
   constexpr int RB = step_row_bytes(G);
-  const int n = k.rows_op / kRowGroup * GB / 1024;  // 1 KB loads of the operand's share
-  const int per = n / 2;                              // of which this wavefront's half
-  const uint32_t base_lds = G == 1 ? k.op_lds6 : k.op_lds;
+  const int n = rows / kRowGroup * GB / 1024;  // 1 KB loads of the operand's share
 #pragma unroll
-  for (int p = 0; p < kCodeLoads; ++p) {
-    const int li = k.half * per + p % per;  // load within the operand's share (repeats past `per`)
-    const int x = li * 1024 + lane * 16;     // this lane's byte within the share
+  for (int p = 0; p < N; ++p) {
+    int li = wave * n / 4 + p;  // load within the operand's share
+    li = li < n ? li : n - 1;
+    const int x = li * 1024 + lane * 16;  // this lane's byte within the share
     int grp = x / GB;
     const int within = x - grp * GB;
     grp = grp < k.last ? grp : k.last;  // row groups past the padded rows re-read the last one
-    cur.doff[p] = (uint32_t)(grp * kRowGroup * RB + within);
-    cur.mo[p] = uni(base_lds + (uint32_t)li * 1024u);
+    doff[p] = (uint32_t)(grp * kRowGroup * RB + within);
+    mo[p] = uni((G == 1 ? k.lds6 : k.lds) + (uint32_t)li * 1024u);
   }
+}
+
+template <int BN, int BM>
+using Cursor = DmaCursor<Tile<BN, BM>::kLoadsW, Tile<BN, BM>::kLoadsX>;
+
+template <int G, int BN, int BM>
+__device__ __forceinline__ void group_offsets(const DmaConst& k, Cursor<BN, BM>& cur, int lane) {
+  operand_offsets<G, Tile<BN, BM>::kLoadsW>(k.w, BN, k.wave, cur.wdoff, cur.wmo, lane);
+  operand_offsets<G, Tile<BN, BM>::kLoadsX>(k.x, BM, k.wave, cur.xdoff, cur.xmo, lane);
 }
 
 // Stage boundaries: group 0 is [0, q1), group 1 [q1, q2), group 2 [q2, Q);
@@ -219,111 +232,73 @@ struct Stages {
 
 __device__ __forceinline__ int stage_group(const Stages& S, int q) { return q < S.q1 ? 0 : (q < S.q2 ? 1 : 2); }
 
-// Point the cursor at the first stage of group g (global stage index q).
-__device__ __forceinline__ void cursor_group(const DmaConst& k, const Stages& S, DmaCursor& cur, int g, int q,
-                                             int lane) {
-  cur.g = g;
-  cur.q = q;
-  cur.u = 0;
-  if (g == 0)
-    cur.bc = uni(k.code0);
-  else if (g == 1)
-    cur.bc = uni(k.code1);
-  else
-    cur.bc = uni(k.code2);
-  cur.bs = uni(k.sc + (int64_t)(g == 0 ? 0 : (g == 1 ? S.t1 : S.t2)) * k.sstride);
-  if (g == 0)
-    group_offsets<0>(k, cur, lane);
-  else if (g == 1)
-    group_offsets<1>(k, cur, lane);
-  else
-    group_offsets<2>(k, cur, lane);
+// Point the cursor at the s-th stage of group G: its bases, the group's offsets
+// and the increments to the stages after it.
+template <int G, int BN, int BM>
+__device__ __forceinline__ void cursor_group(const DmaConst& k, const Stages& S, Cursor<BN, BM>& cur, int s, int lane) {
+  const int64_t ws = G == 0 ? k.w.rstride0 : (G == 1 ? k.w.rstride1 : k.w.rstride2);
+  const int64_t xs = G == 0 ? k.x.rstride0 : (G == 1 ? k.x.rstride1 : k.x.rstride2);
+  const int step = G == 0 ? s : s >> 1;
+  const int u = G == 0 ? 0 : s & 1;
+  const int64_t half = stage_grp_bytes(G);  // to the second half of a step (E3M2 / E4M3)
+  cur.u = u;
+  cur.bw = uni((G == 0 ? k.w.code0 : (G == 1 ? k.w.code1 : k.w.code2)) + step * ws + u * half);
+  cur.bx = uni((G == 0 ? k.x.code0 : (G == 1 ? k.x.code1 : k.x.code2)) + step * xs + u * half);
+  cur.bs = uni(k.sc + (int64_t)((G == 0 ? 0 : (G == 1 ? S.t1 : S.t2)) + step) * k.sstride);
+  cur.winc0 = G == 0 ? ws : half;
+  cur.winc1 = G == 0 ? ws : ws - half;
+  cur.xinc0 = G == 0 ? xs : half;
+  cur.xinc1 = G == 0 ? xs : xs - half;
+  cur.sinc0 = G == 0 ? k.sstride : 0;
+  cur.sinc1 = k.sstride;
+  cur.flip = G == 0 ? 0 : 1;
+  group_offsets<G, BN, BM>(k, cur, lane);
 }
 
-// Advance the cursor past the stage it points at (it stays on the last
-// stage once there).
-__device__ __forceinline__ void cursor_next(const DmaConst& k, const Stages& S, DmaCursor& cur, int lane) {
-  const int nq = cur.q + 1;
-  if (nq >= S.Q) return;
-  const int ng = stage_group(S, nq);
-  if (ng != cur.g) {
-    cursor_group(k, S, cur, ng, nq, lane);
-    return;
-  }
-  cur.q = nq;
-  if (cur.g == 0) {
-    cur.bc += k.rstride0;
-    cur.bs += k.sstride;
-  } else if (cur.u == 0) {
-    cur.bc += cur.g == 1 ? stage_grp_bytes(1) : stage_grp_bytes(2);
-    cur.u = 1;
-  } else {
-    if (cur.g == 1)
-      cur.bc += k.rstride1 - stage_grp_bytes(1);
-    else
-      cur.bc += k.rstride2 - stage_grp_bytes(2);
-    cur.bs += k.sstride;
-    cur.u = 0;
-  }
-  cur.bc = uni(cur.bc);
-  cur.bs = uni(cur.bs);
+// Point the cursor at stage q.
+template <int BN, int BM>
+__device__ __forceinline__ void cursor_at(const DmaConst& k, const Stages& S, Cursor<BN, BM>& cur, int q, int lane) {
+  if (q < S.q1)
+    cursor_group<0, BN, BM>(k, S, cur, q, lane);
+  else if (q < S.q2)
+    cursor_group<1, BN, BM>(k, S, cur, q - S.q1, lane);
+  else
+    cursor_group<2, BN, BM>(k, S, cur, q - S.q2, lane);
+}
+
+// One stage on inside a group: no branch, the offsets untouched.
+template <int NW, int NX>
+__device__ __forceinline__ void cursor_step(DmaCursor<NW, NX>& cur) {
+  cur.bw = uni(cur.bw + (cur.u ? cur.winc1 : cur.winc0));
+  cur.bx = uni(cur.bx + (cur.u ? cur.xinc1 : cur.xinc0));
+  cur.bs = uni(cur.bs + (cur.u ? cur.sinc1 : cur.sinc0));
+  cur.u ^= cur.flip;
 }
 
 // Point the cursor at stage qr for a run of stages whose refills stay in
 // qr's group (hold = true: every refill of the run is qr itself, the last
 // stage).  Only here do the group's per-lane offsets change.
-__device__ __forceinline__ void cursor_segment(const DmaConst& k, const Stages& S, DmaCursor& cur, int qr, bool hold,
+template <int BN, int BM>
+__device__ __forceinline__ void cursor_segment(const DmaConst& k, const Stages& S, Cursor<BN, BM>& cur, int qr, bool hold,
                                                int lane) {
-  const int g = stage_group(S, qr);
-  cursor_group(k, S, cur, g, qr, lane);  // the group's first stage, u = 0
-  if (g == 0) {
-    cur.bc = uni(cur.bc + (int64_t)qr * k.rstride0);
-    cur.bs = uni(cur.bs + (int64_t)qr * k.sstride);
-    cur.inc0 = cur.inc1 = k.rstride0;
-    cur.sinc0 = cur.sinc1 = k.sstride;
-    cur.flip = 0;
-  } else {
-    const int s = qr - (g == 1 ? S.q1 : S.q2);
-    const int64_t rs = g == 1 ? k.rstride1 : k.rstride2;
-    const int64_t gb = g == 1 ? stage_grp_bytes(1) : stage_grp_bytes(2);
-    cur.bc = uni(cur.bc + (int64_t)(s >> 1) * rs + (s & 1) * gb);
-    cur.bs = uni(cur.bs + (int64_t)(s >> 1) * k.sstride);
-    cur.u = s & 1;
-    cur.inc0 = gb;
-    cur.inc1 = rs - gb;
-    cur.sinc0 = 0;
-    cur.sinc1 = k.sstride;
-    cur.flip = 1;
-  }
+  cursor_at<BN, BM>(k, S, cur, qr, lane);
   if (hold) {
-    cur.inc0 = cur.inc1 = cur.sinc0 = cur.sinc1 = 0;
+    cur.winc0 = cur.winc1 = cur.xinc0 = cur.xinc1 = cur.sinc0 = cur.sinc1 = 0;
     cur.flip = 0;
   }
-}
-
-// One stage on inside a segment: no branch, the offsets untouched.
-__device__ __forceinline__ void cursor_step(DmaCursor& cur) {
-  cur.bc = uni(cur.bc + (cur.u ? cur.inc1 : cur.inc0));
-  cur.bs = uni(cur.bs + (cur.u ? cur.sinc1 : cur.sinc0));
-  cur.u ^= cur.flip;
 }
 
 // Load P of the stage the cursor points at, into the slot at LDS byte
-// address st: code loads 0..7, then the scale load (P = 8).
-template <int P>
-__device__ __forceinline__ void issue_load(const DmaConst& k, const DmaCursor& cur, uint32_t st) {
-  if constexpr (P < kCodeLoads)
-    dma16_s(cur.doff[P], cur.bc, st + cur.mo[P]);
+// address st: the weight rows' codes, the activation rows', the scales.
+template <int P, int BN, int BM>
+__device__ __forceinline__ void issue_load(const DmaConst& k, const Cursor<BN, BM>& cur, uint32_t st) {
+  using T = Tile<BN, BM>;
+  if constexpr (P < T::kLoadsW)
+    dma16_s(cur.wdoff[P], cur.bw, st + cur.wmo[P]);
+  else if constexpr (P < T::kCodeLoads)
+    dma16_s(cur.xdoff[P - T::kLoadsW], cur.bx, st + cur.xmo[P - T::kLoadsW]);
   else
     dma16_masked(k.soff, cur.bs, st + k.sdst, k.smask);
-}
-
-template <int P = 0>
-__device__ __forceinline__ void issue_all(const DmaConst& k, const DmaCursor& cur, uint32_t st) {
-  if constexpr (P < kLoads) {
-    issue_load<P>(k, cur, st);
-    issue_all<P + 1>(k, cur, st);
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -417,11 +392,11 @@ __device__ __forceinline__ v8i operand(const v8i& f) {
 }
 
 // Loads P0 .. P1-1 of the refill.
-template <int P0, int P1>
-__device__ __forceinline__ void issue_loads(const DmaConst& k, const DmaCursor& cur, uint32_t st) {
+template <int P0, int P1, int BN, int BM>
+__device__ __forceinline__ void issue_loads(const DmaConst& k, const Cursor<BN, BM>& cur, uint32_t st) {
   if constexpr (P0 < P1) {
-    issue_load<P0>(k, cur, st);
-    issue_loads<P0 + 1, P1>(k, cur, st);
+    issue_load<P0, BN, BM>(k, cur, st);
+    issue_loads<P0 + 1, P1, BN, BM>(k, cur, st);
   }
 }
 
@@ -444,16 +419,17 @@ struct StageWork {
 // stage starts).
 template <int G, int PN, int FS, int T, int BN, int BM>
 __device__ __forceinline__ void mfma_block(Acc<BN, BM>& acc, const Ops<BN, BM>& o, const int* sc, Ops<BN, BM>& nxt,
-                                           const DmaConst& k, const DmaCursor& cur, const StageWork& w) {
+                                           const DmaConst& k, const Cursor<BN, BM>& cur, const StageWork& w) {
   constexpr int TN = Tile<BN, BM>::TN, TM = Tile<BN, BM>::TM;
   constexpr int kPer = TN * TM;
   constexpr int kM = stage_slices(G) * kPer;
+  constexpr int kLoads = Tile<BN, BM>::kLoads;
   if constexpr (T < kM) {
     constexpr int fmt = group_fmt(G, FS);
     constexpr int KK = T / kPer, i = (T % kPer) / TM, j = T % TM;
     acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand<G, KK>(o.f[i]), operand<G, KK>(o.f[TN + j]),
                                                                 acc[i][j], fmt, fmt, 2 * KK, sc[i], 2 * KK, sc[TN + j]);
-    issue_loads<(T * kLoads + kM - 1) / kM, ((T + 1) * kLoads + kM - 1) / kM>(k, cur, w.st_refill);
+    issue_loads<(T * kLoads + kM - 1) / kM, ((T + 1) * kLoads + kM - 1) / kM, BN, BM>(k, cur, w.st_refill);
     constexpr int kSpan = kM * 3 / 4;
     constexpr int kItems = 2 * Tile<BN, BM>::F;
     if constexpr (T < kSpan) read_items<PN, T * kItems / kSpan, (T + 1) * kItems / kSpan>(nxt, w.ad);
@@ -475,7 +451,7 @@ struct Ctx {
 // `nxt` (with group G's pattern: for the group's last stage those reads are
 // of no use, harmlessly, and the next group reads its first stage again).
 template <int G, int FS, int BN, int BM>
-__device__ __forceinline__ void stage(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, DmaCursor& dc, uint32_t& st, int q,
+__device__ __forceinline__ void stage(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Cursor<BN, BM>& dc, uint32_t& st, int q,
                                       const Ops<BN, BM>& cur, Ops<BN, BM>& nxt) {
   using T = Tile<BN, BM>;
   constexpr int NS = T::kSlots;
@@ -490,7 +466,7 @@ __device__ __forceinline__ void stage(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Dm
   // the NS - 2 stages after q+1 may still be in flight), everyone's reads of
   // stage q's slot are done
   wait_lgkm0();
-  wait_vmcnt<(NS - 2) * kLoads>();
+  wait_vmcnt<(NS - 2) * T::kLoads>();
   barrier();
   const uint32_t st_end = c.lds0 + NS * T::kSlotBytes;
   const uint32_t st_next = st + T::kSlotBytes < st_end ? st + T::kSlotBytes : c.lds0;
@@ -500,7 +476,7 @@ __device__ __forceinline__ void stage(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Dm
   // the cursor moves on before the MFMAs (straight-line: a branch there
   // would end the MFMAs' basic block and let them sink away from the work
   // they are interleaved with); this stage's refill uses the position it had
-  const DmaCursor issue = dc;
+  const Cursor<BN, BM> issue = dc;
   cursor_step(dc);
   mfma_block<G, pattern(G), FS, 0>(acc, cur, sc, nxt, c.k, issue, w);
   st = st_next;
@@ -511,7 +487,7 @@ __device__ __forceinline__ void stage(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Dm
 // wavefront has passed the barrier after it, and st is its slot; on exit
 // the same holds for the next group's first stage.
 template <int G, int FS, int BN, int BM>
-__device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, DmaCursor& dc, uint32_t& st) {
+__device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Cursor<BN, BM>& dc, uint32_t& st) {
   using T = Tile<BN, BM>;
   const int qb = G == 0 ? 0 : (G == 1 ? c.S.q1 : c.S.q2);
   const int qe = G == 0 ? c.S.q1 : (G == 1 ? c.S.q2 : c.S.Q);
@@ -535,7 +511,7 @@ __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc
       if (S.Q - 1 - NS < e) e = S.Q - 1 - NS;
     }
     e = e > q ? e : q + 1;
-    cursor_segment(c.k, S, dc, qr, hold, c.lane);
+    cursor_segment<BN, BM>(c.k, S, dc, qr, hold, c.lane);
     for (; q + 1 < e; q += 2) {
       stage<G, FS>(c, acc, dc, st, q, A, B);
       stage<G, FS>(c, acc, dc, st, q + 1, B, A);
@@ -586,30 +562,32 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiled_kernel(GemmArgs a, int
   c.S.t1 = a.steps[0];
   c.S.t2 = a.steps[0] + a.steps[1];
 
-  // this wavefront's loads: wavefronts 0-1 the weight rows, 2-3 the
-  // activation rows, each one half of the operand's share of a stage
   DmaConst& k = c.k;
-  k.op = wave >> 1;
-  k.half = wave & 1;
-  k.rows_op = k.op ? BM : BN;
-  const Operand& o = k.op ? a.x : a.w;
-  const int64_t r0 = k.op ? m0 : n0;  // the tile's first row of the operand (below its padded rows - 31)
-  k.code0 = o.q[0] + r0 * step_row_bytes(0);
-  k.code1 = o.q[1] + r0 * step_row_bytes(1);
-  k.code2 = o.q[2] + r0 * step_row_bytes(2);
-  k.rstride0 = o.rp * step_row_bytes(0);
-  k.rstride1 = o.rp * step_row_bytes(1);
-  k.rstride2 = o.rp * step_row_bytes(2);
-  k.last = (int)(o.rp / kRowGroup - r0 / kRowGroup - 1);
-  k.op_lds = k.op ? BN / kRowGroup * 2048 : 0;
-  k.op_lds6 = k.op ? BN / kRowGroup * 1536 : 0;
+  k.wave = wave;
+  auto codes = [&](DmaCodes& d, const Operand& o, int64_t r0) {  // r0: the tile's first row (below its padded rows - 31)
+    d.code0 = o.q[0] + r0 * step_row_bytes(0);
+    d.code1 = o.q[1] + r0 * step_row_bytes(1);
+    d.code2 = o.q[2] + r0 * step_row_bytes(2);
+    d.rstride0 = o.rp * step_row_bytes(0);
+    d.rstride1 = o.rp * step_row_bytes(1);
+    d.rstride2 = o.rp * step_row_bytes(2);
+    d.last = (int)(o.rp / kRowGroup - r0 / kRowGroup - 1);
+  };
+  codes(k.w, a.w, n0);
+  codes(k.x, a.x, m0);
+  k.w.lds = k.w.lds6 = 0;
+  k.x.lds = BN / kRowGroup * 2048;
+  k.x.lds6 = BN / kRowGroup * 1536;
+  const int op = wave >> 1, half = wave & 1;  // of the scale load: wavefronts 0-1 the weight rows, 2-3 the activation rows
+  const Operand& o = op ? a.x : a.w;
+  const int64_t r0 = op ? m0 : n0;
   // scale words (4 bytes per row and step): one half of the operand's rows,
   // 4 rows per lane; rows past the padded rows re-read the last 4
-  const int per = k.rows_op / 2;
-  int64_t row = k.half * per + c.lane * 4;  // row within the tile
+  const int per = (op ? BM : BN) / 2;
+  int64_t row = half * per + c.lane * 4;  // row within the tile
   row = r0 + row + 4 <= o.rp ? row : o.rp - 4 - r0;
   k.soff = (uint32_t)row * kStepBlocks;
-  k.sdst = (uint32_t)(T::kScaleOff + (k.op ? BN * kStepBlocks : 0) + k.half * per * kStepBlocks);
+  k.sdst = (uint32_t)(T::kScaleOff + (op ? BN * kStepBlocks : 0) + half * per * kStepBlocks);
   k.smask = per / 4 >= 64 ? ~0ull : ((1ull << (per / 4)) - 1);
   k.sc = o.sc + r0 * kStepBlocks;
   k.sstride = o.rp * kStepBlocks;
@@ -623,14 +601,14 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiled_kernel(GemmArgs a, int
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
 
   // fill the ring (issues past the last stage repeat it), wait for stage 0
-  DmaCursor dc;
-  const int g0 = stage_group(c.S, 0);
-  cursor_group(k, c.S, dc, g0, 0, c.lane);
+  Cursor<BN, BM> dc;
   for (int q = 0; q < NS; ++q) {
-    issue_all(k, dc, __builtin_amdgcn_readfirstlane(c.lds0 + q * T::kSlotBytes));
-    cursor_next(k, c.S, dc, c.lane);
+    const int qi = q < c.S.Q ? q : c.S.Q - 1;
+    if (q == 0 || qi == c.S.q1 || qi == c.S.q2) cursor_at<BN, BM>(k, c.S, dc, qi, c.lane);
+    issue_loads<0, T::kLoads, BN, BM>(k, dc, __builtin_amdgcn_readfirstlane(c.lds0 + q * T::kSlotBytes));
+    if (qi + 1 < c.S.Q) cursor_step(dc);
   }
-  wait_vmcnt<(NS - 1) * kLoads>();
+  wait_vmcnt<(NS - 1) * T::kLoads>();
   barrier();
 
   // the K loop, group by group
