@@ -408,7 +408,7 @@ static hipError_t launch_split(const GemmArgs& a, hipStream_t stream) {
 // CU between workgroups, which the figures include).  From 64 .. 512 rows x
 // K = 1024, 4096, 14336, 27648 x N = 4096 .. 14336; e.g. 2 x 2 at K = 4096:
 // 6.9 us for up to 256 tiles, 12.6 for 512; the LDS-tiled 256 x 128 tile
-// 21-25 us up to 256 tiles, 46-50 for 512.
+// 17.7-22.8 us up to 256 tiles, 38.6-42 for 512.
 struct Shape {
   int tn, tm, once, round;
   double step;
@@ -416,7 +416,7 @@ struct Shape {
 static const Shape kShapes[] = {
     {1, 1, 330, 20, 4.5}, {2, 1, 340, 20, 6.7}, {2, 2, 120, 180, 10.5}, {2, 3, 200, 220, 14.5}, {2, 4, 200, 330, 16.8},
 };
-static const Shape kTiled = {8, 4, 0, 700, 40.0};  // the LDS-tiled kernel's 256 x 128 tile
+static const Shape kTiled = {8, 4, 0, 520, 36.5};  // the LDS-tiled kernel's 256 x 128 tile
 
 static double shape_cost(const Shape& s, int64_t rows_n, int64_t rows_m, double steps, int cus) {
   const int64_t tiles = ((rows_n + 32 * s.tn - 1) / (32 * s.tn)) * ((rows_m + 32 * s.tm - 1) / (32 * s.tm));

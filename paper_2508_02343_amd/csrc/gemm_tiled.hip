@@ -23,28 +23,37 @@
 // The ring runs on across group boundaries, so the next group's first
 // stages are in flight while the current group finishes.
 //
-// Every wavefront issues the same number of loads for every stage: eight
-// 1 KB code loads (wavefronts 0-1 the weight rows, 2-3 the activation rows;
-// a share smaller than eight loads is completed by loading its last pieces
-// again, into the same LDS bytes with the same data) and one scale load.
-// The vmcnt wait for a stage is then one constant, and issuing the next
-// stage is a loop-carried cursor (one base pointer per wavefront, per-lane
-// offsets fixed per group) instead of per-stage address arithmetic, which
-// a single wavefront per SIMD could not hide behind its MFMAs.  The K loop
-// runs in segments whose refills stay in one group: inside a segment the
-// cursor only adds a precomputed increment (no branch, its per-lane offsets
-// untouched), and it is re-pointed between segments; with the group change
-// tested every stage, the scalar bookkeeping of a stage outweighed its
-// MFMAs (5-10 % slower).
+// Every loading wavefront issues the same number of loads for every stage: a
+// quarter of the weight rows' codes, a quarter of the activation rows' and one
+// scale load (a share with fewer pieces is completed by loading its last ones
+// again, into the same LDS bytes with the same data).  The vmcnt wait for a
+// stage is then one constant, and issuing the next stage is a cursor (base
+// pointers, per-lane offsets fixed per group) instead of per-stage address
+// arithmetic.  (With wavefronts 0-1 on the weight rows and 2-3 on half as many
+// activation rows, the latter repeated half of their loads at 256 x 128.)
 //
-// Per stage q: wait for this wavefront's LDS reads and for its loads of
-// stage q+1, one s_barrier (everyone's part of stage q+1 has landed and
-// every read of stage q's slot is done); then the stage's MFMAs, each
-// followed by its share of the other work: the loads that refill stage q's
-// slot with stage q + slots, and the LDS reads of stage q+1's operands.
-// The sched_barrier fences keep that order.  Workgroups are mapped to tiles
+// 256 x 128: four more wavefronts, the producers, do the loading (produce).
+// 256 x 256: the registers allow one wavefront per SIMD, which loads and
+// multiplies; the K loop runs in segments whose refills stay in one group:
+// inside a segment the cursor only adds a precomputed increment (no branch,
+// its per-lane offsets untouched), and it is re-pointed between segments; with
+// the group change tested every stage, the scalar bookkeeping of a stage
+// outweighed its MFMAs (5-10 % slower).
+//
+// Per stage q: its MFMAs, each followed by its share of the other work: the
+// loads that refill stage q's slot with stage q + slots (256 x 256), the LDS
+// reads of stage q+1's operands, and shortly before the end one s_barrier
+// behind waits for these reads and for stage q+2's loads (mfma_block).  The
+// sched_barrier fences keep that order.  Workgroups are mapped to tiles
 // XCD by XCD and in groups of weight tiles, so the tiles that run together
 // on one XCD share its L2.
+//
+// Measured (us, M x N x K): without the producers and with the waits between
+// the stages 2048 x 4096 x 4096 took 29.9 (now 27.0), 1000 x 4096 x 5400 in
+// E2M3 / E5M2 30.1 (26.6), 700 x 4096 x 14336 44.0 (39.4); the 256 x 256 tile
+// 4096 x 4096 x 14336 150 (148.5), 8192 x 5120 x 27648 640 (636): that one is
+// at the card's power limit (all-zero codes: 507).  The MFMAs alone, without
+// loads and LDS reads: 19.0 (2048 x 4096 x 4096), 430 (8192 x 5120 x 27648).
 #include "gemm_common.hpp"
 
 namespace mm {
@@ -52,8 +61,7 @@ namespace mm {
 namespace tiled {
 
 constexpr int kLdsBytes = 160 * 1024;
-constexpr int kWaves = 4;
-constexpr int kThreads = 64 * kWaves;
+constexpr int kWaves = 4;  // wavefronts with accumulators, one per SIMD
 
 // A stage of group G: E2M1 one layout step (two 64-channel slices), E3M2 and
 // E4M3 half a step (one slice).
@@ -72,10 +80,15 @@ struct Tile {
   static constexpr int kRows = BN + BM;
   static constexpr int kScaleOff = kRows * 64;  // scale words follow the largest code payload (64 B per row)
   static constexpr int kSlotBytes = kScaleOff + kRows * kStepBlocks;
-  // four slots for both shapes: the 256 x 128 tile fits six, but with four
-  // its K loop starts after four stages instead of six and it measured 2-4 %
-  // faster (2048 x 4096 x 4096: 30.8 -> 30.1 us)
-  static constexpr int kSlots = 4;
+  // The 256 x 128 tile leaves each SIMD the registers of a second wavefront:
+  // four producer wavefronts then issue the loads.  A load occupies the CU's
+  // texture-address path for about 20 cycles, 560-600 cycles for a stage's 32
+  // against 512 of its MFMAs, and a wavefront that issues both in order has its
+  // MFMAs wait behind its loads (stage times on 2048 x 4096 x 4096: MFMAs
+  // alone 275 ns, with the LDS reads 410, with the loads 390, with both 540).
+  static constexpr bool kProducers = BM == 128;
+  static constexpr int kThreads = 64 * kWaves * (kProducers ? 2 : 1);
+  static constexpr int kSlots = kProducers ? 6 : 4;
   // a wavefront's loads of a stage: a quarter of each operand's codes, and a
   // scale load
   static constexpr int kLoadsW = BN / 64, kLoadsX = BM / 64;
@@ -400,44 +413,6 @@ __device__ __forceinline__ void issue_loads(const DmaConst& k, const Cursor<BN, 
   }
 }
 
-// Everything a stage does beside its MFMAs.
-struct StageWork {
-  uint32_t st_refill;  // slot being refilled (stage q's)
-  OpsAddr ad;          // reads of stage q+1
-};
-
-// The MFMAs of one group-G stage (acc += W x X^T), in program order: E2M1
-// runs its first slice over every accumulator, then its second (so no MFMA
-// waits for the one before it).  Lane 32 g + r needs the scale of block
-// 2 kk' + g of its row, kk' the slice's 64-channel position in the layout
-// step: sc holds the scale words shifted right by 8 g (+ 16 for the second
-// half of an E3M2 / E4M3 step) and op_sel picks byte 2 kk (kk the slice
-// within the stage).  Each MFMA is followed by its share of the refill's
-// loads (all kLoads of them spread over the stage's MFMAs, however many
-// there are) and of the reads of the next stage (pattern PN, spread over the
-// first three quarters of the MFMAs so that they have landed when the next
-// stage starts).
-template <int G, int PN, int FS, int T, int BN, int BM>
-__device__ __forceinline__ void mfma_block(Acc<BN, BM>& acc, const Ops<BN, BM>& o, const int* sc, Ops<BN, BM>& nxt,
-                                           const DmaConst& k, const Cursor<BN, BM>& cur, const StageWork& w) {
-  constexpr int TN = Tile<BN, BM>::TN, TM = Tile<BN, BM>::TM;
-  constexpr int kPer = TN * TM;
-  constexpr int kM = stage_slices(G) * kPer;
-  constexpr int kLoads = Tile<BN, BM>::kLoads;
-  if constexpr (T < kM) {
-    constexpr int fmt = group_fmt(G, FS);
-    constexpr int KK = T / kPer, i = (T % kPer) / TM, j = T % TM;
-    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand<G, KK>(o.f[i]), operand<G, KK>(o.f[TN + j]),
-                                                                acc[i][j], fmt, fmt, 2 * KK, sc[i], 2 * KK, sc[TN + j]);
-    issue_loads<(T * kLoads + kM - 1) / kM, ((T + 1) * kLoads + kM - 1) / kM, BN, BM>(k, cur, w.st_refill);
-    constexpr int kSpan = kM * 3 / 4;
-    constexpr int kItems = 2 * Tile<BN, BM>::F;
-    if constexpr (T < kSpan) read_items<PN, T * kItems / kSpan, (T + 1) * kItems / kSpan>(nxt, w.ad);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_block<G, PN, FS, T + 1>(acc, o, sc, nxt, k, cur, w);
-  }
-}
-
 // Kernel-wide state of one tile.
 template <int BN, int BM>
 struct Ctx {
@@ -447,47 +422,92 @@ struct Ctx {
   int wn0, wm0, lane;
 };
 
-// Stage q of group G: its operands are in `cur`, stage q+1's are read into
-// `nxt` (with group G's pattern: for the group's last stage those reads are
-// of no use, harmlessly, and the next group reads its first stage again).
-template <int G, int FS, int BN, int BM>
-__device__ __forceinline__ void stage(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Cursor<BN, BM>& dc, uint32_t& st, int q,
-                                      const Ops<BN, BM>& cur, Ops<BN, BM>& nxt) {
-  using T = Tile<BN, BM>;
-  constexpr int NS = T::kSlots;
-  const Stages& S = c.S;
-  // scale operands: shift by 8 g, + 16 for the second half of an E3M2 / E4M3 step
-  const int u = G == 0 ? 0 : ((q - (G == 1 ? S.q1 : S.q2)) & 1);
-  const int shift = 8 * (c.lane >> 5) + 16 * u;
-  int sc[T::F];
+// What moves on from stage to stage: the slot in use, the LDS addresses of the
+// next stage's reads, the DMA cursor and the next stage's scale shift.
+template <int BN, int BM>
+struct Loop {
+  uint32_t st;     // slot of the stage whose MFMAs run
+  OpsAddr ad;      // reads of the stage after it
+  Cursor<BN, BM> dma;
+  int shift;       // 8 g, + 16 in the second half of an E3M2 / E4M3 step, of the stage after it
+};
+
+// Shift scale words F0 .. F1-1 down to what their lanes feed the MFMA.
+template <int F0, int F1, int BN, int BM>
+__device__ __forceinline__ void shift_scales(Ops<BN, BM>& o, int shift) {
 #pragma unroll
-  for (int f = 0; f < T::F; ++f) sc[f] = (int)((uint32_t)cur.s[f] >> shift);
-  // stage q+1 landed (this wavefront's loads: every stage issues kLoads, and
-  // the NS - 2 stages after q+1 may still be in flight), everyone's reads of
-  // stage q's slot are done
-  wait_lgkm0();
-  wait_vmcnt<(NS - 2) * T::kLoads>();
-  barrier();
-  const uint32_t st_end = c.lds0 + NS * T::kSlotBytes;
-  const uint32_t st_next = st + T::kSlotBytes < st_end ? st + T::kSlotBytes : c.lds0;
-  StageWork w;
-  w.st_refill = __builtin_amdgcn_readfirstlane(st);
-  w.ad = ops_addr<pattern(G), BN, BM>(st_next, opaque_s(c.wn0), opaque_s(c.wm0), c.lane);
-  // the cursor moves on before the MFMAs (straight-line: a branch there
-  // would end the MFMAs' basic block and let them sink away from the work
-  // they are interleaved with); this stage's refill uses the position it had
-  const Cursor<BN, BM> issue = dc;
-  cursor_step(dc);
-  mfma_block<G, pattern(G), FS, 0>(acc, cur, sc, nxt, c.k, issue, w);
-  st = st_next;
+  for (int f = F0; f < F1; ++f) o.s[f] = (int)((uint32_t)o.s[f] >> shift);
+}
+
+// The MFMAs of one group-G stage q (acc += W x X^T), in program order: E2M1
+// runs its first slice over every accumulator, then its second (so no MFMA
+// waits for the one before it).  Lane 32 g + r needs the scale of block
+// 2 kk' + g of its row, kk' the slice's 64-channel position in the layout
+// step: o.s holds the scale words shifted right by 8 g (+ 16 for the second
+// half of an E3M2 / E4M3 step) and op_sel picks byte 2 kk (kk the slice
+// within the stage).
+//
+// Everything else the stage does goes out behind one of its MFMAs, so that
+// between two stages' MFMAs nothing is left to issue (with the cursor, the
+// addresses, the scale shifts and the waits between the stages, the matrix
+// cores idled for 200-400 cycles of each):
+//  - the first three quarters (kR): the loads that refill stage q's slot and
+//    the reads of stage q+1 (for the group's last stage they are of no use,
+//    harmlessly, and the next group reads its first stage again);
+//  - then the cursor's and the addresses' step to the next stage;
+//  - three MFMAs before the end the synchronisation that the next stage
+//    needs: this wavefront's reads of stage q+1 are done (its slot is
+//    refilled next), its loads of stage q+2 have landed (every stage issues
+//    kLoads, and the NS - 2 stages after q+2 may still be in flight), and so
+//    for everyone at the barrier;
+//  - behind the last two, stage q+1's scale shifts.
+template <int G, int FS, int T, int BN, int BM>
+__device__ __forceinline__ void mfma_block(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, const Ops<BN, BM>& o,
+                                           Ops<BN, BM>& nxt, Loop<BN, BM>& l) {
+  using Ti = Tile<BN, BM>;
+  constexpr int TN = Ti::TN, TM = Ti::TM, F = Ti::F, NS = Ti::kSlots;
+  constexpr int kPer = TN * TM;
+  constexpr int kM = stage_slices(G) * kPer;
+  constexpr int kR = kM == 8 ? 4 : kM * 3 / 4, kS = kM - 3;
+  if constexpr (T < kM) {
+    constexpr int fmt = group_fmt(G, FS);
+    constexpr int KK = T / kPer, i = (T % kPer) / TM, j = T % TM;
+    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand<G, KK>(o.f[i]), operand<G, KK>(o.f[TN + j]),
+                                                                acc[i][j], fmt, fmt, 2 * KK, o.s[i], 2 * KK, o.s[TN + j]);
+    if constexpr (T < kR) {
+      constexpr int kLoads = Ti::kLoads, kItems = 2 * F;
+      if constexpr (!Ti::kProducers)
+        issue_loads<(T * kLoads + kR - 1) / kR, ((T + 1) * kLoads + kR - 1) / kR, BN, BM>(c.k, l.dma, l.st);
+      read_items<pattern(G), T * kItems / kR, (T + 1) * kItems / kR>(nxt, l.ad);
+    }
+    if constexpr (T == kR && !Ti::kProducers) cursor_step(l.dma);
+    if constexpr (T == kR + 1) {
+      const uint32_t st_end = c.lds0 + NS * Ti::kSlotBytes;
+      l.st = uni(l.st + Ti::kSlotBytes < st_end ? l.st + Ti::kSlotBytes : c.lds0);
+      const uint32_t after = l.st + Ti::kSlotBytes < st_end ? l.st + Ti::kSlotBytes : c.lds0;
+      l.ad = ops_addr<pattern(G), BN, BM>(after, opaque_s(c.wn0), opaque_s(c.wm0), c.lane);
+    }
+    if constexpr (T == kS) {
+      wait_lgkm0();
+      if constexpr (!Ti::kProducers) wait_vmcnt<(NS - 2) * Ti::kLoads>();
+      barrier();
+    }
+    if constexpr (T == kM - 2) shift_scales<0, F / 2>(nxt, l.shift);
+    if constexpr (T == kM - 1) {
+      shift_scales<F / 2, F>(nxt, l.shift);
+      if constexpr (G >= 1) l.shift ^= 16;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    mfma_block<G, FS, T + 1>(c, acc, o, nxt, l);
+  }
 }
 
 // All stages of group G, two per iteration (the operand registers
-// alternate).  On entry the group's first stage has landed and every
-// wavefront has passed the barrier after it, and st is its slot; on exit
-// the same holds for the next group's first stage.
+// alternate).  On entry the group's first two stages have landed for everyone
+// and l.st is the first one's slot; on exit the same holds for the next
+// group's.
 template <int G, int FS, int BN, int BM>
-__device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Cursor<BN, BM>& dc, uint32_t& st) {
+__device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Loop<BN, BM>& l) {
   using T = Tile<BN, BM>;
   const int qb = G == 0 ? 0 : (G == 1 ? c.S.q1 : c.S.q2);
   const int qe = G == 0 ? c.S.q1 : (G == 1 ? c.S.q2 : c.S.Q);
@@ -495,7 +515,23 @@ __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc
   constexpr int NS = T::kSlots;
   const Stages& S = c.S;
   Ops<BN, BM> A, B;
-  read_items<pattern(G), 0, 2 * T::F>(A, ops_addr<pattern(G), BN, BM>(st, c.wn0, c.wm0, c.lane));
+  read_items<pattern(G), 0, 2 * T::F>(A, ops_addr<pattern(G), BN, BM>(l.st, c.wn0, c.wm0, c.lane));
+  const uint32_t after = l.st + T::kSlotBytes < c.lds0 + NS * T::kSlotBytes ? l.st + T::kSlotBytes : c.lds0;
+  l.ad = ops_addr<pattern(G), BN, BM>(after, c.wn0, c.wm0, c.lane);
+  l.shift = 8 * (c.lane >> 5);
+  shift_scales<0, T::F>(A, l.shift);
+  if constexpr (G >= 1) l.shift ^= 16;
+  wait_lgkm0();
+  barrier();  // everyone has read the first stage: its slot may be refilled
+  if constexpr (T::kProducers) {
+    int q = qb;
+    for (; q + 1 < qe; q += 2) {
+      mfma_block<G, FS, 0>(c, acc, A, B, l);
+      mfma_block<G, FS, 0>(c, acc, B, A, l);
+    }
+    if (q < qe) mfma_block<G, FS, 0>(c, acc, A, B, l);
+    return;
+  }
   // segments: runs of stages whose refills (stage q + NS, the last one
   // again past the end) stay in one group, so that inside a run the cursor
   // only steps; it is re-pointed between runs
@@ -511,16 +547,68 @@ __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc
       if (S.Q - 1 - NS < e) e = S.Q - 1 - NS;
     }
     e = e > q ? e : q + 1;
-    cursor_segment<BN, BM>(c.k, S, dc, qr, hold, c.lane);
+    cursor_segment<BN, BM>(c.k, S, l.dma, qr, hold, c.lane);
     for (; q + 1 < e; q += 2) {
-      stage<G, FS>(c, acc, dc, st, q, A, B);
-      stage<G, FS>(c, acc, dc, st, q + 1, B, A);
+      mfma_block<G, FS, 0>(c, acc, A, B, l);
+      mfma_block<G, FS, 0>(c, acc, B, A, l);
     }
     if (q < e) {
-      stage<G, FS>(c, acc, dc, st, q, A, B);
+      mfma_block<G, FS, 0>(c, acc, A, B, l);
       A = B;  // the next run starts from A
       ++q;
     }
+  }
+}
+
+// Fill the ring (issues past the last stage repeat it) and wait for the first
+// two stages.
+template <int BN, int BM>
+__device__ __forceinline__ void fill_ring(const Ctx<BN, BM>& c, Cursor<BN, BM>& cur) {
+  using T = Tile<BN, BM>;
+  for (int q = 0; q < T::kSlots; ++q) {
+    const int qi = q < c.S.Q ? q : c.S.Q - 1;
+    if (q == 0 || qi == c.S.q1 || qi == c.S.q2) cursor_at<BN, BM>(c.k, c.S, cur, qi, c.lane);
+    issue_loads<0, T::kLoads, BN, BM>(c.k, cur, uni(c.lds0 + q * T::kSlotBytes));
+    if (qi + 1 < c.S.Q) cursor_step(cur);
+  }
+  wait_vmcnt<(T::kSlots - 2) * T::kLoads>();
+  barrier();
+}
+
+// A producer wavefront: after each barrier behind which a stage's slot is free
+// (everyone has read the stage) the loads of the stage kSlots on, then its own
+// loads of the stage two on have landed, and the barrier that says so.  The
+// barriers are those of run_group.  The K loop starts behind the first kStart
+// stages; the rest of the ring fills two stages at a time behind the first
+// ones (filled whole at the start, it held the K loop back by 1 us).
+template <int BN, int BM>
+__device__ __forceinline__ void produce(const Ctx<BN, BM>& c) {
+  using T = Tile<BN, BM>;
+  constexpr int NS = T::kSlots, L = T::kLoads, kStart = 3;
+  static_assert(NS == 2 * kStart, "three turns of two stages reach the steady distance");
+  Cursor<BN, BM> cur;
+  uint32_t st = c.lds0;
+  int s = 0;  // next stage to issue (past the end the last one again)
+  auto issue = [&]() {
+    const int qi = s < c.S.Q ? s : c.S.Q - 1;
+    if (s == 0 || qi == c.S.q1 || qi == c.S.q2) cursor_at<BN, BM>(c.k, c.S, cur, qi, c.lane);
+    issue_loads<0, L, BN, BM>(c.k, cur, uni(st));
+    if (qi + 1 < c.S.Q) cursor_step(cur);
+    st = st + T::kSlotBytes < c.lds0 + NS * T::kSlotBytes ? st + T::kSlotBytes : c.lds0;
+    ++s;
+  };
+  for (int k = 0; k < kStart; ++k) issue();
+  wait_vmcnt<(kStart - 2) * L>();
+  barrier();
+  for (int q = 0; q < c.S.Q; ++q) {
+    if (q == 0 || q == c.S.q1 || q == c.S.q2) barrier();  // a group's first stage has been read
+    if (q < kStart) issue();  // into a slot that no stage has used yet, or one free since the last barrier
+    issue();
+    // stage q + 2 has landed: the stages issued after it may be in flight
+    if (q == 0) wait_vmcnt<2 * L>();
+    else if (q == 1) wait_vmcnt<3 * L>();
+    else wait_vmcnt<(NS - 2) * L>();
+    barrier();
   }
 }
 
@@ -529,9 +617,8 @@ __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc
 using namespace tiled;
 
 template <int BN, int BM, int FS>
-__global__ __launch_bounds__(kThreads, 1) void gemm_tiled_kernel(GemmArgs a, int tiles_n, int tiles_m) {
+__global__ __launch_bounds__((Tile<BN, BM>::kThreads), 1) void gemm_tiled_kernel(GemmArgs a, int tiles_n, int tiles_m) {
   using T = Tile<BN, BM>;
-  constexpr int NS = T::kSlots;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   constexpr int kGroupN = 4;  // weight tiles that share an XCD's L2 at a time
 
@@ -553,8 +640,9 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiled_kernel(GemmArgs a, int
   Ctx<BN, BM> c;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: keeps DMA setup scalar
   c.lane = threadIdx.x & 63;
-  c.wn0 = (wave & 1) * T::WN;
-  c.wm0 = (wave >> 1) * T::WM;
+  const int w4 = T::kProducers ? wave & 3 : wave;  // (producers: which quarter of the loads)
+  c.wn0 = (w4 & 1) * T::WN;
+  c.wm0 = (w4 >> 1) * T::WM;
   c.lds0 = lds_addr(lds);
   c.S.q1 = a.steps[0];
   c.S.q2 = c.S.q1 + 2 * a.steps[1];
@@ -563,7 +651,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiled_kernel(GemmArgs a, int
   c.S.t2 = a.steps[0] + a.steps[1];
 
   DmaConst& k = c.k;
-  k.wave = wave;
+  k.wave = w4;
   auto codes = [&](DmaCodes& d, const Operand& o, int64_t r0) {  // r0: the tile's first row (below its padded rows - 31)
     d.code0 = o.q[0] + r0 * step_row_bytes(0);
     d.code1 = o.q[1] + r0 * step_row_bytes(1);
@@ -578,7 +666,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiled_kernel(GemmArgs a, int
   k.w.lds = k.w.lds6 = 0;
   k.x.lds = BN / kRowGroup * 2048;
   k.x.lds6 = BN / kRowGroup * 1536;
-  const int op = wave >> 1, half = wave & 1;  // of the scale load: wavefronts 0-1 the weight rows, 2-3 the activation rows
+  const int op = w4 >> 1, half = w4 & 1;  // of the scale load: wavefronts 0-1 the weight rows, 2-3 the activation rows
   const Operand& o = op ? a.x : a.w;
   const int64_t r0 = op ? m0 : n0;
   // scale words (4 bytes per row and step): one half of the operand's rows,
@@ -600,22 +688,19 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiled_kernel(GemmArgs a, int
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
 
-  // fill the ring (issues past the last stage repeat it), wait for stage 0
-  Cursor<BN, BM> dc;
-  for (int q = 0; q < NS; ++q) {
-    const int qi = q < c.S.Q ? q : c.S.Q - 1;
-    if (q == 0 || qi == c.S.q1 || qi == c.S.q2) cursor_at<BN, BM>(k, c.S, dc, qi, c.lane);
-    issue_loads<0, T::kLoads, BN, BM>(k, dc, __builtin_amdgcn_readfirstlane(c.lds0 + q * T::kSlotBytes));
-    if (qi + 1 < c.S.Q) cursor_step(dc);
+  const bool producer = T::kProducers && wave >= kWaves;
+  if (producer) {
+    if constexpr (T::kProducers) produce(c);
+  } else {
+    // the K loop, group by group
+    Loop<BN, BM> l;
+    if constexpr (T::kProducers) barrier();  // the ring's first two stages have landed
+    else fill_ring(c, l.dma);
+    l.st = uni(c.lds0);
+    run_group<0, FS>(c, acc, l);
+    run_group<1, FS>(c, acc, l);
+    run_group<2, FS>(c, acc, l);
   }
-  wait_vmcnt<(NS - 1) * T::kLoads>();
-  barrier();
-
-  // the K loop, group by group
-  uint32_t st = c.lds0;
-  run_group<0, FS>(c, acc, dc, st);
-  run_group<1, FS>(c, acc, dc, st);
-  run_group<2, FS>(c, acc, dc, st);
 
   // Epilogue: every load and read of the ring is done (the last stages
   // issued repeats of the last one); the bf16 tile is assembled in LDS and
@@ -630,25 +715,27 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_tiled_kernel(GemmArgs a, int
   constexpr int kRowStride = BN * 2 + 16;
   static_assert(BM * kRowStride <= kLdsBytes, "epilogue tile fits LDS");
   const int r = c.lane & 31, g = c.lane >> 5;
+  if (!producer) {
 #pragma unroll
-  for (int i = 0; i < T::TN; ++i)
+    for (int i = 0; i < T::TN; ++i)
 #pragma unroll
-    for (int j = 0; j < T::TM; ++j) {
+      for (int j = 0; j < T::TM; ++j) {
 #pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        const uint32_t lo = pack_bf16x2_rne(acc[i][j][4 * h], acc[i][j][4 * h + 1]);
-        const uint32_t hi = pack_bf16x2_rne(acc[i][j][4 * h + 2], acc[i][j][4 * h + 3]);
-        const uint32_t at = c.lds0 + (c.wm0 + 32 * j + r) * kRowStride + (c.wn0 + 32 * i + 8 * h + 4 * g) * 2;
-        *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)at) = u32x2{lo, hi};
+        for (int h = 0; h < 4; ++h) {
+          const uint32_t lo = pack_bf16x2_rne(acc[i][j][4 * h], acc[i][j][4 * h + 1]);
+          const uint32_t hi = pack_bf16x2_rne(acc[i][j][4 * h + 2], acc[i][j][4 * h + 3]);
+          const uint32_t at = c.lds0 + (c.wm0 + 32 * j + r) * kRowStride + (c.wn0 + 32 * i + 8 * h + 4 * g) * 2;
+          *reinterpret_cast<__attribute__((address_space(3))) u32x2*>((uintptr_t)at) = u32x2{lo, hi};
+        }
+        // one accumulator tile at a time: keeps the VGPR copies of the
+        // accumulators few
+        __builtin_amdgcn_sched_barrier(0);
       }
-      // one accumulator tile at a time: keeps the VGPR copies of the
-      // accumulators few
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  }
   __syncthreads();
   constexpr int kChunks = BN / 8;  // 16-byte chunks per row
   const int64_t M = a.x.rows, N = a.w.rows;
-  for (int ch = threadIdx.x; ch < BM * kChunks; ch += kThreads) {
+  for (int ch = threadIdx.x; ch < BM * kChunks; ch += T::kThreads) {
     const int rr = ch / kChunks, col = (ch - rr * kChunks) * 8;
     const int64_t m = m0 + rr, n = n0 + col;
     if (m >= M || n >= N) continue;
@@ -677,7 +764,7 @@ static hipError_t launch_tile_fs(const GemmArgs& a, hipStream_t stream) {
     attr_set = true;
   }
   const int tn = (int)((a.w.rows + BN - 1) / BN), tm = (int)((a.x.rows + BM - 1) / BM);
-  hipLaunchKernelGGL((gemm_tiled_kernel<BN, BM, FS>), dim3((unsigned)(tn * tm)), dim3(kThreads), kLdsBytes, stream, a,
+  hipLaunchKernelGGL((gemm_tiled_kernel<BN, BM, FS>), dim3((unsigned)(tn * tm)), dim3(Tile<BN, BM>::kThreads), kLdsBytes, stream, a,
                      tn, tm);
   return hipGetLastError();
 }

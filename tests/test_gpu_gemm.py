@@ -68,6 +68,28 @@ def test_ragged(M, N, split):
     _check_full(xb, wb, perm, split, f"M{M} N{N} {split}")
 
 
+@pytest.mark.parametrize("formats", [("E3M2", "E4M3"), ("E2M3", "E5M2")], ids="-".join)
+@pytest.mark.parametrize("M,N,split", [(1990, 4050, (32, 0, 0)), (2000, 4040, (0, 0, 96)), (1921, 3841, (160, 32, 64)),
+                                       (2040, 4090, (640, 96, 160)), (1985, 4089, (1152, 0, 0)),
+                                       (4000, 4090, (32, 0, 32)), (3841, 4001, (640, 224, 96))], ids=str)
+def test_tiled_few_stages(M, N, split, formats):
+    """The LDS-tiled kernel's ring with fewer stages than slots, as many and a
+    few more, groups of one stage and groups that change while the ring fills:
+    256 x 128 tiles (loads by producer wavefronts) and, from one 256 x 256 tile
+    per CU, those."""
+    note(f"tiled M={M} N={N} split={split} {formats}")
+    xb, wb, perm = _rand_case(M, N, split, seed=M + N + split[0])
+    b = _b()
+    p = to_dev_perm(perm)
+    a = b.quantize_act(to_dev_bf16(xb), p, split, formats=formats)
+    w = b.quantize_weight(to_dev_bf16(wb), p, split, formats=formats)
+    y = b.gemm(a, w)
+    torch.cuda.synchronize()
+    fm = (O.E2M1, O.FORMATS[formats[0]], O.FORMATS[formats[1]])
+    ra, rw = O.quantize_mixed(xb, perm, split, fm), O.quantize_mixed(wb, perm, split, fm)
+    assert_gemm_close(y_to_f64(y), O.gemm_mixed(ra, rw), ctx=f"{formats} M{M} N{N} {split}")
+
+
 @pytest.mark.parametrize("M,N,split", [(1, 6001, (96, 160, 96)), (20, 6000, (256, 128, 128)),
                                        (50, 6000, (0, 0, 512)), (1, 12000, (256, 128, 128)),
                                        (20, 12000, (96, 160, 96)), (50, 12000, (256, 128, 128)),
