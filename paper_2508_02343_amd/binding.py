@@ -133,7 +133,7 @@ def layout_sizes(rows: int, K: int, split) -> dict:
     return {"q4": sz.q4, "q6": sz.q6, "q8": sz.q8, "sc": sz.sc}
 
 
-@functools.lru_cache(maxsize=1024)
+@functools.lru_cache(maxsize=1024, typed=True)
 def _buffer_sizes(rows: int, K: int, split: tuple) -> tuple:
     """layout_sizes as (q4, q6, q8, sc), remembered by value."""
     sz = layout_sizes(rows, K, split)
@@ -214,12 +214,13 @@ class MXTensor:
 def _check_mx(t: MXTensor, rows: int, K: int, split, device, name: str) -> None:
     """An MXTensor whose buffers hold the packed layout of (rows, K, split)
     on `device` (the library reads and writes exactly those bytes)."""
-    if t.rows != rows or t.K != K or (t.split != split and tuple(map(int, t.split)) != tuple(map(int, split))):
+    split = tuple(map(int, split))
+    if t.rows != rows or t.K != K or tuple(map(int, t.split)) != split:
         raise ValueError(f"{name} is [{t.rows}, {t.K}] split {tuple(t.split)}, expected [{rows}, {K}] split "
-                         f"{tuple(split)}")
+                         f"{split}")
     index = -1 if device.type == "cpu" else device.index  # (comparing devices costs four times as much)
     bufs = (t.q4, t.q6, t.q8, t.sc)
-    for buf, need in zip(bufs, _buffer_sizes(rows, K, split if type(split) is tuple else tuple(map(int, split)))):
+    for buf, need in zip(bufs, _buffer_sizes(rows, K, split)):
         if (need > 0) if buf is None else (buf.nbytes < need or buf.get_device() != index or not buf.is_contiguous()):
             b = ("q4", "q6", "q8", "sc")[[x is buf for x in bufs].index(True)]
             n = 0 if buf is None else buf.nbytes

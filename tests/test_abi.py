@@ -9,7 +9,9 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
+import torch
 
 # a missing or unloadable library fails this module (no skip): the binding
 # raises ImportError when libmicromix.so is absent
@@ -156,6 +158,19 @@ def test_binding_descriptor_fields():
     assert t.q4.numel() == 2048 and t.sc.numel() == 512
     e = b.MXTensor.empty(3, 64, (64, 0, 0), device="cpu").descriptor()
     assert e.q6 is None and e.q8 is None
+
+
+@pytest.mark.parametrize("as_split", [list, np.array, torch.tensor])
+def test_split_may_be_any_sequence(as_split):
+    """A descriptor's split as a list, an array or a tensor counts by its values."""
+    t = b.MXTensor.empty(5, 352, (96, 160, 96), device="cpu")
+    t.split = as_split([96, 160, 96])
+    cpu = t.sc.device
+    b._check_mx(t, 5, 352, t.split, cpu, "t")
+    b._check_mx(t, 5, 352, (96, 160, 96), cpu, "t")
+    assert t._packed() == bytes(t.descriptor())
+    with pytest.raises(ValueError):
+        b._check_mx(t, 5, 352, (96, 96, 160), cpu, "t")
 
 
 def test_descriptor_layout_matches_the_header():
