@@ -265,15 +265,16 @@ __device__ __forceinline__ double wave_sums(const double (&v)[N], int lane) {
   return __builtin_bit_cast(double, (uint64_t)h32[0] << 32 | l32[0]) + __builtin_bit_cast(double, (uint64_t)h32[1] << 32 | l32[1]);
 }
 
-// fp32(1 / sqrt(m)), m > 0 and normal, evaluated in fp64: the hardware's
-// reciprocal square root estimate and two Newton steps (relative error below
-// 2^-51, as a square root and a division have) instead of their
-// long expansions, which every thread of a row would run.
+// fp32(1 / sqrt(m)), m > 0 and normal or infinite, evaluated in fp64: the
+// hardware's reciprocal square root estimate and two Newton steps (relative
+// error below 2^-51, as a square root and a division have) instead of their
+// long expansions, which every thread of a row would run.  A row with an
+// infinite element keeps the estimate's zero (the steps would give a NaN).
 __device__ __forceinline__ float rsqrt_f64(double m) {
   double y = __builtin_amdgcn_rsq(m);
 #pragma unroll
   for (int i = 0; i < 2; ++i) y = fma(y * 0.5, fma(-m * y, y, 1.0), y);
-  return (float)y;
+  return m == __builtin_inf() ? 0.0f : (float)y;
 }
 
 // 32-bit LDS addresses

@@ -92,6 +92,26 @@ def _gamma(K, seed):
     return f32_bits((1.0 + 0.25 * rng.standard_normal(K)).astype(np.float32))
 
 
+def test_infinite_element():
+    """An infinite element makes its row's factor zero: every other block of
+    the row quantises signed zeros, and other rows are not touched."""
+    K, split = 4096, (2048, 1024, 1024)
+    rng = np.random.default_rng(5)
+    xb, gb = f32_bits(rng.standard_normal((5, K)).astype(np.float32)), _gamma(K, 5)
+    r32 = _factors(xb, 1e-5)[0]
+    y = O.rmsnorm_apply(xb, gb, np.where(np.arange(5) == 2, np.float32(0), r32))
+    xb[2, -1] = 0x7F80
+    perm = np.arange(K, dtype=np.int32)
+    out = _run(xb, gb, 1e-5, perm, split)
+    got, ref = PL.untile(out.raw_host(), out.rows, out.split), O.quantize_mixed(y, perm, split)
+    for name, skip in (("q4", 0), ("q6", 0), ("q8", 32), ("sc", 1)):  # (the infinity's own block)
+        g, r = got[name], np.asarray(getattr(ref, name))
+        rows = np.arange(5) != 2
+        assert np.array_equal(g[rows], r[rows]), name
+        n = r.shape[1] - skip
+        assert np.array_equal(g[2, :n], r[2, :n]), name
+
+
 RAGGED = [(96, 160, 96), (352, 0, 0), (0, 352, 0), (0, 0, 352), (32, 32, 288)]
 
 
