@@ -14,8 +14,13 @@ namespace {
 
 constexpr int64_t kMaxQuantK = 32768;  // one row of bf16 must fit the LDS budget
 constexpr int64_t kMaxRows = (int64_t)1 << 31;
-// Up to this many activation rows (one 16-row tile) the decode kernel may run.
-constexpr int64_t kDirectMaxM = 16;
+// Up to this many activation rows (two 16-row tiles) the decode kernel may
+// run: it has a strip of weight rows for every CU where the K-splitting
+// kernel's 32-row tiles have one for every second.  Weights from HBM, 75 / 18.75
+// / 6.25 % split, decode kernel against the K-splitting one (us, N x K): 20 rows
+// 4096 x 4096 5.2 / 6.7, 6144 x 4096 6.3 / 7.9; 32 rows 4096 x 14336 10.9 / 14.5,
+// 14336 x 4096 9.3 / 8.9; 64 rows 4096 x 4096 6.9 / 5.7, 1024 x 4096 6.3 / 4.9.
+constexpr int64_t kDirectMaxM = 32;
 // ... unless the weight is larger than this and not mostly 8-bit codes: the
 // K-splitting kernel streams long weights faster (us, 8 rows, decode kernel
 // against it: 28672 x 4096 mixed, 71 MB, 15.7 / 12.7, E2M1 62 MB 12.9 / 11.4;

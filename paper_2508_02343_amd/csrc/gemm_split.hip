@@ -1,6 +1,6 @@
 // Mixed MX GEMM for the shapes between decode and prefill (batched decode,
 // prompt chunks, few weight rows): too many activation rows for the decode
-// kernel's 16-row tiles, too few output tiles for the LDS-tiled kernel to give
+// kernel's one or two 16-row tiles, too few output tiles for the LDS-tiled kernel to give
 // every CU one.
 //
 // What bounds these shapes is how many CUs share the operand stream, and the

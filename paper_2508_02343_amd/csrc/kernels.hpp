@@ -99,7 +99,7 @@ hipError_t launch_calibrate(const CalibArgs& a, hipStream_t stream);
 // with hipGetSymbolAddress on the first call on each device, with that
 // device current, and cached per device.  Allocates nothing.
 hipError_t calibrate_scratch(void** ptr);
-hipError_t launch_gemm_direct(const GemmArgs& a, hipStream_t stream);  // at most 16 activation rows
+hipError_t launch_gemm_direct(const GemmArgs& a, hipStream_t stream);  // at most 32 activation rows
 hipError_t launch_gemm_tiled(const GemmArgs& a, hipStream_t stream);
 // The K-splitting kernel's tile shape for these operands (-1: none, the tiled
 // kernel is faster), and the kernel with that shape.
