@@ -219,13 +219,11 @@ def _check_mx(t: MXTensor, rows: int, K: int, split, device, name: str) -> None:
         raise ValueError(f"{name} is [{t.rows}, {t.K}] split {tuple(t.split)}, expected [{rows}, {K}] split "
                          f"{split}")
     index = -1 if device.type == "cpu" else device.index  # (comparing devices costs four times as much)
-    bufs = (t.q4, t.q6, t.q8, t.sc)
-    for buf, need in zip(bufs, _buffer_sizes(rows, K, split)):
-        if (need > 0) if buf is None else (buf.nbytes < need or buf.get_device() != index or not buf.is_contiguous()):
-            b = ("q4", "q6", "q8", "sc")[[x is buf for x in bufs].index(True)]
-            n = 0 if buf is None else buf.nbytes
-            if n < need:
-                raise ValueError(f"{name}.{b} holds {n} bytes, the layout needs {need}")
+    for b, buf, need in zip(("q4", "q6", "q8", "sc"), (t.q4, t.q6, t.q8, t.sc), _buffer_sizes(rows, K, split)):
+        n = 0 if buf is None else buf.nbytes
+        if n < need:
+            raise ValueError(f"{name}.{b} holds {n} bytes, the layout needs {need}")
+        if buf is not None and (buf.get_device() != index or not buf.is_contiguous()):
             raise ValueError(f"{name}.{b} must be contiguous and on {device}")
 
 

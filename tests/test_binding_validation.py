@@ -33,6 +33,22 @@ def test_short_buffer_rejected():
         b._check_mx(t, 40, 128, SPLIT, torch.device("cpu"), "out")
 
 
+def test_missing_buffer_is_named():
+    """A missing buffer is reported by its own name, also behind an empty group."""
+    t = _mx(40, 352, (256, 0, 96))
+    t.q8 = None
+    with pytest.raises(ValueError, match=r"t\.q8 holds 0 bytes"):
+        b._check_mx(t, 40, 352, (256, 0, 96), torch.device("cpu"), "t")
+
+
+def test_short_shared_buffer_is_named():
+    """Two groups that share one buffer: the one that is too long for it is reported."""
+    t = _mx(40, 256, (64, 0, 192))
+    t.q8 = t.q4
+    with pytest.raises(ValueError, match=r"t\.q8 holds"):
+        b._check_mx(t, 40, 256, (64, 0, 192), torch.device("cpu"), "t")
+
+
 def test_host_input_rejected():
     x = torch.zeros(40, 128, dtype=torch.bfloat16)
     perm = torch.arange(128, dtype=torch.int32)
