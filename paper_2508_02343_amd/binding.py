@@ -133,11 +133,18 @@ def layout_sizes(rows: int, K: int, split) -> dict:
     return {"q4": sz.q4, "q6": sz.q6, "q8": sz.q8, "sc": sz.sc}
 
 
-@functools.lru_cache(maxsize=1024, typed=True)
-def _buffer_sizes(rows: int, K: int, split: tuple) -> tuple:
-    """layout_sizes as (q4, q6, q8, sc), remembered by value."""
-    sz = layout_sizes(rows, K, split)
-    return sz["q4"], sz["q6"], sz["q8"], sz["sc"]
+def _fresh_sizes(rows, K, split) -> tuple:
+    """layout_sizes as (q4, q6, q8, sc)."""
+    return tuple(layout_sizes(rows, K, split).values())
+
+
+_known_sizes = functools.lru_cache(maxsize=1024)(_fresh_sizes)
+
+
+def _buffer_sizes(rows, K, split) -> tuple:
+    """The same, remembered by value: for plain whole numbers only (an array or
+    a tensor can change, and hashes by identity or not at all)."""
+    return (_known_sizes if type(rows) is type(K) is int else _fresh_sizes)(rows, K, split)
 
 
 def _stream_ptr(stream) -> ctypes.c_void_p:

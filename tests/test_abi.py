@@ -173,6 +173,27 @@ def test_split_may_be_any_sequence(as_split):
         b._check_mx(t, 5, 352, (96, 96, 160), cpu, "t")
 
 
+@pytest.mark.parametrize("as_count", [np.array, torch.tensor, np.int64])
+def test_row_count_may_be_any_whole_number(as_count):
+    """A row count given as an array or a tensor counts by its present value:
+    after it has grown, buffers of the old size are too short."""
+    rows, split = as_count(40), (96, 160, 96)
+    t = b.MXTensor.empty(rows, 352, split, device="cpu")
+    assert t.q4.numel() == b.layout_sizes(40, 352, split)["q4"]
+    b._check_mx(t, t.rows, 352, split, t.sc.device, "t")
+    if as_count is np.int64:
+        return
+    rows += 40
+    assert b.MXTensor.empty(rows, 352, split, device="cpu").q4.numel() == b.layout_sizes(80, 352, split)["q4"]
+    with pytest.raises(ValueError, match=r"t\.q4 holds"):
+        b._check_mx(t, t.rows, 352, split, t.sc.device, "t")
+
+
+def test_fractional_row_count_is_refused():
+    with pytest.raises(ctypes.ArgumentError):
+        b.MXTensor.empty(40.0, 352, (96, 160, 96), device="cpu")
+
+
 def test_descriptor_layout_matches_the_header():
     """The ctypes mirror has the C struct's size and field offsets (checked
     against a C compiler's view of include/micromix.h)."""
