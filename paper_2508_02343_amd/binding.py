@@ -153,12 +153,21 @@ def _stream_ptr(stream) -> ctypes.c_void_p:
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+# torch's own accessors behind current_stream(), where this torch has them
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_int(stream) -> int:
     """The hipStream_t to launch on, without making a Stream object for the
-    current one (3 us)."""
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return stream.cuda_stream
+    current one (3 us).  current_stream() initialises torch's GPU state, and
+    refuses where that is impossible (a forked child of a process that uses the
+    GPU), so it is asked unless that state is up."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 @dataclass

@@ -70,3 +70,24 @@ def test_gemm_result_dtype_and_stride_rejected():
         b.gemm(a, w, y=torch.empty(40, 48, dtype=torch.float32))
     with pytest.raises(ValueError):
         b.gemm(a, w, y=torch.empty(48, 40, dtype=torch.bfloat16).t())
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_raw_device", None])
+def test_current_stream_without_the_raw_accessors(monkeypatch, missing):
+    """Where torch lacks the raw accessors, or its GPU state is not up (no
+    initialisation yet, a forked child), torch.cuda.current_stream() decides."""
+
+    def never(*_):
+        raise AssertionError("raw accessor called")
+
+    class Stream:
+        cuda_stream = 1234
+
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.setattr(torch._C, name, never, raising=False)
+    for name in ("_raw_stream", "_raw_device"):
+        monkeypatch.setattr(b, name, None if name == missing else never, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: missing is not None)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    assert b._stream_int(None) == 1234
+    assert b._stream_int(Stream()) == 1234
