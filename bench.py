@@ -65,7 +65,7 @@ def gemm_bytes(M: int, N: int, K: int, split) -> int:
 # sources each GEMM kernel is compiled from (a committed counter summary is
 # used only while they are unchanged)
 GEMM_SOURCES = {"tiled": ("gemm_tiled.hip", "gemm_common.hpp", "mx_device.hpp", "kernels.hpp"),
-                "direct": ("gemm_direct.hip", "gemm_split.hip", "gemm_common.hpp", "mx_device.hpp",
+                "direct": ("gemm_direct.hip", "gemm_split.hip", "gemm_route.hpp", "gemm_common.hpp", "mx_device.hpp",
                            "kernels.hpp")}
 CALIB_BYTES = 256 << 20  # plain copy used to calibrate the FETCH_SIZE / WRITE_SIZE counters
 

@@ -8,26 +8,13 @@
 #include <cstring>
 
 #include "../../include/micromix.h"
+#include "gemm_route.hpp"
 #include "kernels.hpp"
 
 namespace {
 
 constexpr int64_t kMaxQuantK = 32768;  // one row of bf16 must fit the LDS budget
 constexpr int64_t kMaxRows = (int64_t)1 << 31;
-// Up to this many activation rows (two 16-row tiles) the decode kernel may
-// run: it has a strip of weight rows for every CU where the K-splitting
-// kernel's 32-row tiles have one for every second.  Weights from HBM, 75 / 18.75
-// / 6.25 % split, decode kernel against the K-splitting one (us, N x K): 20 rows
-// 4096 x 4096 5.2 / 6.7, 6144 x 4096 6.3 / 7.9; 32 rows 4096 x 14336 10.9 / 14.5,
-// 14336 x 4096 9.3 / 8.9; 64 rows 4096 x 4096 6.9 / 5.7, 1024 x 4096 6.3 / 4.9.
-constexpr int64_t kDirectMaxM = 32;
-// ... unless the weight is larger than this and not mostly 8-bit codes: the
-// K-splitting kernel streams long weights faster (us, 8 rows, decode kernel
-// against it: 28672 x 4096 mixed, 71 MB, 15.7 / 12.7, E2M1 62 MB 12.9 / 11.4;
-// 5120 x 27648 mixed, 86 MB, 23.0 / 18.4), the decode kernel the short ones
-// (14336 x 4096 mixed, 36 MB, 8.2 / 8.1; 4096 x 4096, 10 MB, 4.4 / 4.7) and
-// E4M3 (28672 x 4096, 21.3 / 23.5; 5120 x 27648, 34 / 38).
-constexpr int64_t kDirectMaxWeight = 40ll << 20;
 // Calibration workspace: the workgroup maxima (nchunks * tiles <= 256 words)
 // and the per-block group counts (2 * K / 256 <= 256 words), then fp64
 // partial sums and means, then int32 per-slice rank counts.
@@ -186,14 +173,18 @@ mm::Operand operand(const mm_mx_tensor* t) {
   return o;
 }
 
-hipError_t launch_gemm(const mm::GemmArgs& g, const Layout& w, hipStream_t s) {
-  const int64_t bytes = w.bytes[0] + w.bytes[1] + w.bytes[2];
-  if (g.x.rows <= kDirectMaxM && (bytes <= kDirectMaxWeight || 2 * w.bytes[2] > bytes))
-    return mm::launch_gemm_direct(g, s);
-  int shape = -1;
-  hipError_t e = mm::choose_gemm_split(g, &shape);
+hipError_t launch_gemm(const mm::GemmArgs& g, hipStream_t s) {
+  mm::GemmSizes z = {g.x.rows, g.w.rows, {g.steps[0], g.steps[1], g.steps[2]}, 0};
+  hipError_t e = mm::device_cus(&z.cus);
   if (e != hipSuccess) return e;
-  return shape >= 0 ? mm::launch_gemm_split(g, shape, s) : mm::launch_gemm_tiled(g, s);
+  const mm::GemmRoute r = mm::gemm_route(z);
+  switch (r.kernel) {
+    case mm::GemmKernel::kDirect: return mm::launch_gemm_direct(g, s);
+    case mm::GemmKernel::kSplit: return mm::launch_gemm_split(g, r.shape, s);
+    case mm::GemmKernel::kTiled128: return mm::launch_gemm_tiled(g, false, s);
+    case mm::GemmKernel::kTiled256: return mm::launch_gemm_tiled(g, true, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -259,7 +250,7 @@ mm_status mm_gemm(const mm_mx_tensor* a, const mm_mx_tensor* w, void* y_bf16, in
   g.ldy = ldy;
   g.fs = format_set(a);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_gemm(g, layout(w->rows, w->split), s);
+  hipError_t e = launch_gemm(g, s);
   if (e != hipSuccess) return fail(MM_ERR_DEVICE, "mm_gemm: launch failed: %s", hipGetErrorString(e));
   return MM_OK;
 }

@@ -31,6 +31,7 @@
 // shared out by the groups' bytes, so an output's summation order depends on
 // the split and K only, not on the tile shape.
 #include "gemm_common.hpp"
+#include "gemm_route.hpp"
 
 namespace mm {
 
@@ -401,58 +402,18 @@ static hipError_t launch_split(const GemmArgs& a, hipStream_t stream) {
   return hipErrorInvalidValue;
 }
 
-// Tile shapes (32-row units of weight and activation rows) and their measured
-// cost, in 10 ns, on 256 CUs: a call takes about once + rounds * (round +
-// step * S), S the layout steps weighted by their bytes (an E2M1 step 1), one
-// round the tiles the CUs hold at once, one each (the two small shapes share a
-// CU between workgroups, which the figures include).  From 64 .. 512 rows x
-// K = 1024, 4096, 14336, 27648 x N = 4096 .. 14336; e.g. 2 x 2 at K = 4096:
-// 6.9 us for up to 256 tiles, 12.6 for 512; the LDS-tiled 256 x 128 tile
-// 17.7-22.8 us up to 256 tiles, 38.6-42 for 512.
-struct Shape {
-  int tn, tm, once, round;
-  double step;
-};
-static const Shape kShapes[] = {
-    {1, 1, 330, 20, 4.5}, {2, 1, 340, 20, 6.7}, {2, 2, 120, 180, 10.5}, {2, 3, 200, 220, 14.5}, {2, 4, 200, 330, 16.8},
-};
-static const Shape kTiled = {8, 4, 0, 520, 36.5};  // the LDS-tiled kernel's 256 x 128 tile
-
-static double shape_cost(const Shape& s, int64_t rows_n, int64_t rows_m, double steps, int cus) {
-  const int64_t tiles = ((rows_n + 32 * s.tn - 1) / (32 * s.tn)) * ((rows_m + 32 * s.tm - 1) / (32 * s.tm));
-  return s.once + (double)((tiles + cus - 1) / cus) * (s.round + s.step * steps);
-}
-
-// The cheapest tile shape whose rows the operands have (the padded rows: at
-// least 32 of each), or *shape = -1 where the LDS-tiled kernel is cheaper.
-// Few rows of a 32-row tile used (M <= 16) still pays: the weight is what is
-// read.
-hipError_t choose_gemm_split(const GemmArgs& a, int* shape) {
-  int cus = 0;
-  hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
-  const double steps = a.steps[0] + a.steps[1] * (25.0 / 17) + a.steps[2] * (33.0 / 17);
-  double best = shape_cost(kTiled, a.w.rows, a.x.rows, steps, cus);
-  *shape = -1;
-  for (int i = 0; i < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
-    const Shape& s = kShapes[i];
-    if (32 * s.tn > a.w.rp || 32 * s.tm > a.x.rp) continue;
-    const double c = shape_cost(s, a.w.rows, a.x.rows, steps, cus);
-    if (c < best) {
-      best = c;
-      *shape = i;
-    }
-  }
-  return hipSuccess;
+template <int I>
+static hipError_t launch_shape(const GemmArgs& a, hipStream_t stream) {
+  return launch_split<kSplitShapes[I].tn, kSplitShapes[I].tm>(a, stream);
 }
 
 hipError_t launch_gemm_split(const GemmArgs& a, int shape, hipStream_t stream) {
   switch (shape) {
-    case 0: return launch_split<1, 1>(a, stream);
-    case 1: return launch_split<2, 1>(a, stream);
-    case 2: return launch_split<2, 2>(a, stream);
-    case 3: return launch_split<2, 3>(a, stream);
-    case 4: return launch_split<2, 4>(a, stream);
+    case 0: return launch_shape<0>(a, stream);
+    case 1: return launch_shape<1>(a, stream);
+    case 2: return launch_shape<2>(a, stream);
+    case 3: return launch_shape<3>(a, stream);
+    case 4: return launch_shape<4>(a, stream);
   }
   return hipErrorInvalidValue;
 }

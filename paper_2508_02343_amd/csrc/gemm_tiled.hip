@@ -781,15 +781,8 @@ static hipError_t launch_tile(const GemmArgs& a, hipStream_t stream) {
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm_tiled(const GemmArgs& a, hipStream_t stream) {
-  // 256 x 256 tiles when they give every CU at least one, else 256 x 128
-  // (twice the tiles)
-  int cus = 0;
-  hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
-  const int64_t t256 = ((a.w.rows + 255) / 256) * ((a.x.rows + 255) / 256);
-  if (t256 >= cus) return launch_tile<256, 256>(a, stream);
-  return launch_tile<256, 128>(a, stream);
+hipError_t launch_gemm_tiled(const GemmArgs& a, bool square, hipStream_t stream) {
+  return square ? launch_tile<256, 256>(a, stream) : launch_tile<256, 128>(a, stream);
 }
 
 }  // namespace mm

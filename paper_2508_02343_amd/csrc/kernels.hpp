@@ -100,10 +100,9 @@ hipError_t launch_calibrate(const CalibArgs& a, hipStream_t stream);
 // device current, and cached per device.  Allocates nothing.
 hipError_t calibrate_scratch(void** ptr);
 hipError_t launch_gemm_direct(const GemmArgs& a, hipStream_t stream);  // at most 32 activation rows
-hipError_t launch_gemm_tiled(const GemmArgs& a, hipStream_t stream);
-// The K-splitting kernel's tile shape for these operands (-1: none, the tiled
-// kernel is faster), and the kernel with that shape.
-hipError_t choose_gemm_split(const GemmArgs& a, int* shape);
+hipError_t launch_gemm_tiled(const GemmArgs& a, bool square, hipStream_t stream);  // 256 x 256 tiles, else 256 x 128
+// The K-splitting kernel with a tile shape (an index into kSplitShapes) whose
+// rows the padded operands have.
 hipError_t launch_gemm_split(const GemmArgs& a, int shape, hipStream_t stream);
 // CUs of the current device (cached per thread for the last device).
 hipError_t device_cus(int* cus);
