@@ -503,9 +503,13 @@ __device__ __forceinline__ void mfma_block(const Ctx<BN, BM>& c, Acc<BN, BM>& ac
 }
 
 // All stages of group G, two per iteration (the operand registers
-// alternate).  On entry the group's first two stages have landed for everyone
-// and l.st is the first one's slot; on exit the same holds for the next
-// group's.
+// alternate).  On entry the group's first stage has landed for everyone and
+// l.st is its slot; on exit the same holds for the next group's.  The first
+// MFMAs need the second stage as well: it has landed behind the barrier in
+// front of them.  The cursor is pointed while the first stage's reads run;
+// behind the barrier it held a tile's first MFMAs back by 0.3-0.4 us (us, M x N
+// x K: 768 x 22016 x 128 in E2M1 19.0 -> 18.0, 8192 x 28672 x 128 132.5 -> 127.5,
+// 4096 x 14336 x 4096 149.4 -> 146.4).
 template <int G, int FS, int BN, int BM>
 __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Loop<BN, BM>& l) {
   using T = Tile<BN, BM>;
@@ -519,9 +523,32 @@ __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc
   const uint32_t after = l.st + T::kSlotBytes < c.lds0 + NS * T::kSlotBytes ? l.st + T::kSlotBytes : c.lds0;
   l.ad = ops_addr<pattern(G), BN, BM>(after, c.wn0, c.wm0, c.lane);
   l.shift = 8 * (c.lane >> 5);
+  // segments: runs of stages whose refills (stage q + NS, the last one
+  // again past the end) stay in one group, so that inside a run the cursor
+  // only steps; it is re-pointed between runs.  Points it at stage q's refill and
+  // gives the run's end.
+  auto segment = [&](int q) {
+    const int qr = q + NS < S.Q ? q + NS : S.Q - 1;
+    const bool hold = q + NS >= S.Q - 1;
+    int e = qe;
+    if (!hold) {
+      const int gr = stage_group(S, qr);
+      if (gr == 0 && S.q1 - NS < e) e = S.q1 - NS;
+      if (gr <= 1 && S.q2 - NS < e) e = S.q2 - NS;
+      if (S.Q - 1 - NS < e) e = S.Q - 1 - NS;
+    }
+    cursor_segment<BN, BM>(c.k, S, l.dma, qr, hold, c.lane);
+    return e > q ? e : q + 1;
+  };
+  int e = qe;
+  if constexpr (!T::kProducers) {
+    e = segment(qb);  // (while the reads run)
+    __builtin_amdgcn_sched_barrier(0);
+  }
   shift_scales<0, T::F>(A, l.shift);
   if constexpr (G >= 1) l.shift ^= 16;
   wait_lgkm0();
+  if constexpr (!T::kProducers) wait_vmcnt<(NS - 2) * T::kLoads>();  // (nothing to wait for but at the tile's start)
   barrier();  // everyone has read the first stage: its slot may be refilled
   if constexpr (T::kProducers) {
     int q = qb;
@@ -532,22 +559,8 @@ __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc
     if (q < qe) mfma_block<G, FS, 0>(c, acc, A, B, l);
     return;
   }
-  // segments: runs of stages whose refills (stage q + NS, the last one
-  // again past the end) stay in one group, so that inside a run the cursor
-  // only steps; it is re-pointed between runs
   int q = qb;
-  while (q < qe) {
-    const int qr = q + NS < S.Q ? q + NS : S.Q - 1;
-    const bool hold = q + NS >= S.Q - 1;
-    int e = qe;
-    if (!hold) {
-      const int gr = stage_group(S, qr);
-      if (gr == 0 && S.q1 - NS < e) e = S.q1 - NS;
-      if (gr <= 1 && S.q2 - NS < e) e = S.q2 - NS;
-      if (S.Q - 1 - NS < e) e = S.Q - 1 - NS;
-    }
-    e = e > q ? e : q + 1;
-    cursor_segment<BN, BM>(c.k, S, l.dma, qr, hold, c.lane);
+  while (true) {
     for (; q + 1 < e; q += 2) {
       mfma_block<G, FS, 0>(c, acc, A, B, l);
       mfma_block<G, FS, 0>(c, acc, B, A, l);
@@ -557,11 +570,13 @@ __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc
       A = B;  // the next run starts from A
       ++q;
     }
+    if (q >= qe) break;
+    e = segment(q);
   }
 }
 
 // Fill the ring (issues past the last stage repeat it) and wait for the first
-// two stages.
+// stage.
 template <int BN, int BM>
 __device__ __forceinline__ void fill_ring(const Ctx<BN, BM>& c, Cursor<BN, BM>& cur) {
   using T = Tile<BN, BM>;
@@ -571,7 +586,7 @@ __device__ __forceinline__ void fill_ring(const Ctx<BN, BM>& c, Cursor<BN, BM>& 
     issue_loads<0, T::kLoads, BN, BM>(c.k, cur, uni(c.lds0 + q * T::kSlotBytes));
     if (qi + 1 < c.S.Q) cursor_step(cur);
   }
-  wait_vmcnt<(T::kSlots - 2) * T::kLoads>();
+  wait_vmcnt<(T::kSlots - 1) * T::kLoads>();
   barrier();
 }
 
@@ -598,10 +613,11 @@ __device__ __forceinline__ void produce(const Ctx<BN, BM>& c) {
     ++s;
   };
   for (int k = 0; k < kStart; ++k) issue();
+  wait_vmcnt<(kStart - 1) * L>();
+  barrier();  // the first stage has landed
   wait_vmcnt<(kStart - 2) * L>();
-  barrier();
   for (int q = 0; q < c.S.Q; ++q) {
-    if (q == 0 || q == c.S.q1 || q == c.S.q2) barrier();  // a group's first stage has been read
+    if (q == 0 || q == c.S.q1 || q == c.S.q2) barrier();  // a group's first stage has been read (and at 0 the second has landed)
     if (q < kStart) issue();  // into a slot that no stage has used yet, or one free since the last barrier
     issue();
     // stage q + 2 has landed: the stages issued after it may be in flight
@@ -694,7 +710,7 @@ __global__ __launch_bounds__((Tile<BN, BM>::kThreads), 1) void gemm_tiled_kernel
   } else {
     // the K loop, group by group
     Loop<BN, BM> l;
-    if constexpr (T::kProducers) barrier();  // the ring's first two stages have landed
+    if constexpr (T::kProducers) barrier();  // the ring's first stage has landed
     else fill_ring(c, l.dma);
     l.st = uni(c.lds0);
     run_group<0, FS>(c, acc, l);
