@@ -16,6 +16,7 @@
 // one step) and reach the lanes that feed them to the MFMA through a
 // cross-lane read, instead of one single-byte load per lane and step.
 #include "gemm_common.hpp"
+#include "gemm_route.hpp"
 
 namespace mm {
 
@@ -145,31 +146,11 @@ __global__ __launch_bounds__(64 * W) void gemm_direct_kernel(GemmArgs a, int R, 
   }
 }
 
-// Wavefronts per group: one for each group that has steps, then one at a
-// time to the group whose wavefronts take the most steps each (ties: the
-// wider format), so the longest chain of steps is as short as it can be.
-static void direct_waves(const GemmArgs& a, int W, int* w) {
-  const int* S = a.steps;
-  for (int G = 0; G < 3; ++G) w[G] = S[G] > 0 ? 1 : 0;
-  for (int k = w[0] + w[1] + w[2]; k < W && k > 0; ++k) {
-    int best = -1, most = -1;
-    for (int G = 2; G >= 0; --G) {
-      if (w[G] == 0) continue;
-      const int c = (S[G] + w[G] - 1) / w[G];
-      if (c > most) {
-        most = c;
-        best = G;
-      }
-    }
-    ++w[best];
-  }
-}
-
 template <int TN, int TM, int W, int FS>
 static hipError_t launch_direct_fs(const GemmArgs& a, int R, hipStream_t stream) {
   const dim3 grid((unsigned)((a.w.rows + R - 1) / R), (unsigned)((a.x.rows + 16 * TM - 1) / (16 * TM)));
   int w[3];
-  direct_waves(a, W, w);
+  share_waves(a.steps, kEvenCost, W, w);
   hipLaunchKernelGGL((gemm_direct_kernel<TN, TM, W, FS>), grid, dim3(64 * W), 0, stream, a, R, w[0], w[1], w[2]);
   return hipGetLastError();
 }
@@ -186,37 +167,15 @@ static hipError_t launch_direct(const GemmArgs& a, int R, hipStream_t stream) {
   }
 }
 
-// Rows per workgroup for two activation tiles: the fewest multiple
-// of 8 (at least 16, at most 64) that spreads the weight rows evenly over k
-// workgroups per CU, k as small as that allows, so that every CU streams
-// about the same number of bytes and each activation fragment feeds up to
-// four weight tiles.
-static int direct_rows(int64_t N, int cus) {
-  int64_t k = N / (64 * (int64_t)cus);
-  for (k = k < 1 ? 1 : k;; ++k) {
-    int64_t R = (N + k * cus - 1) / (k * cus);
-    R = (R + 7) / 8 * 8;
-    if (R <= 64) return R < 16 ? 16 : (int)R;
-  }
-}
-
-// One activation tile (M <= 16): a whole 32-row group per workgroup (each
-// step's loads are one contiguous 2 KB record) with four wavefronts when that
-// still gives every CU a strip, else 16-row strips with eight wavefronts.
-// Measured against the even spread above on this tile: 7.7 against 8.3 us
-// (N = 14336, E2M1), equal for E4M3.
 hipError_t launch_gemm_direct(const GemmArgs& a, hipStream_t stream) {
   int cus = 0;
   hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
-  if (a.x.rows <= 16) {
-    if ((a.w.rows + 31) / 32 >= cus) return launch_direct<2, 1, 4>(a, 32, stream);
-    return launch_direct<1, 1, 8>(a, 16, stream);
-  }
-  const int R = direct_rows(a.w.rows, cus);
-  if (R <= 16) return launch_direct<1, 2, 8>(a, R, stream);
-  if (R <= 32) return launch_direct<2, 2, 8>(a, R, stream);
-  return launch_direct<4, 2, 8>(a, R, stream);
+  const DirectPlan p = direct_plan(a.x.rows, a.w.rows, cus);
+  if (a.x.rows <= 16) return p.waves == 4 ? launch_direct<2, 1, 4>(a, p.rows, stream) : launch_direct<1, 1, 8>(a, p.rows, stream);
+  if (p.rows <= 16) return launch_direct<1, 2, 8>(a, p.rows, stream);
+  if (p.rows <= 32) return launch_direct<2, 2, 8>(a, p.rows, stream);
+  return launch_direct<4, 2, 8>(a, p.rows, stream);
 }
 
 }  // namespace mm

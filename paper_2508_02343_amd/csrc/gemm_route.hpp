@@ -1,5 +1,5 @@
-// Which kernel multiplies operands of given sizes.  Host arithmetic only, no
-// HIP: tests compile it by itself.
+// Which kernel multiplies operands of given sizes, and how it shares out the
+// work.  Host arithmetic only, no HIP: tests compile it by itself.
 #pragma once
 
 #include <stdint.h>
@@ -21,66 +21,165 @@ struct GemmSizes {
   int cus;       // CUs of the device
 };
 
-// Tile shapes of the K-splitting kernel (32-row units of weight and activation
-// rows) and their measured cost, in 10 ns, on 256 CUs: a call takes about once +
-// rounds * (round + step * S), S the layout steps weighted by their bytes (an
-// E2M1 step 1), one round the tiles the CUs hold at once, one each (the two
-// small shapes share a CU between workgroups, which the figures include).  From
-// 64 .. 512 rows x K = 1024, 4096, 14336, 27648 x N = 4096 .. 14336; e.g. 2 x 2
-// at K = 4096: 6.9 us for up to 256 tiles, 12.6 for 512; the LDS-tiled 256 x 128
-// tile 17.7-22.8 us up to 256 tiles, 38.6-42 for 512.
-struct SplitShape {
-  int tn, tm, once, round;
-  double step;
-};
-constexpr SplitShape kSplitShapes[] = {
-    {1, 1, 330, 20, 4.5}, {2, 1, 340, 20, 6.7}, {2, 2, 120, 180, 10.5}, {2, 3, 200, 220, 14.5}, {2, 4, 200, 330, 16.8},
-};
-constexpr int kNumSplitShapes = sizeof(kSplitShapes) / sizeof(kSplitShapes[0]);
-constexpr SplitShape kTiledCost = {8, 4, 0, 520, 36.5};  // the LDS-tiled kernel's 256 x 128 tile
-
-// Workgroups of 512 threads in one launch: a grid has less than 2^32 threads.
-constexpr int64_t kMaxSplitTiles = ((int64_t)1 << 23) - 1;
-
-// Up to this many activation rows (two 16-row tiles) the decode kernel may
-// run: it has a strip of weight rows for every CU where the K-splitting
-// kernel's 32-row tiles have one for every second.  Weights from HBM, 75 / 18.75
-// / 6.25 % split, decode kernel against the K-splitting one (us, N x K): 20 rows
-// 4096 x 4096 5.2 / 6.7, 6144 x 4096 6.3 / 7.9; 32 rows 4096 x 14336 10.9 / 14.5,
-// 14336 x 4096 9.3 / 8.9; 64 rows 4096 x 4096 6.9 / 5.7, 1024 x 4096 6.3 / 4.9.
-constexpr int64_t kDirectMaxM = 32;
-// ... unless the weight is larger than this and not mostly 8-bit codes: the
-// K-splitting kernel streams long weights faster (us, 8 rows, decode kernel
-// against it: 28672 x 4096 mixed, 71 MB, 15.7 / 12.7, E2M1 62 MB 12.9 / 11.4;
-// 5120 x 27648 mixed, 86 MB, 23.0 / 18.4), the decode kernel the short ones
-// (14336 x 4096 mixed, 36 MB, 8.2 / 8.1; 4096 x 4096, 10 MB, 4.4 / 4.7) and
-// E4M3 (28672 x 4096, 21.3 / 23.5; 5120 x 27648, 34 / 38).
-constexpr int64_t kDirectMaxWeight = 40ll << 20;
-
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t tile_count(int64_t n, int64_t m, int tn, int tm) { return ceil_div(n, 32 * tn) * ceil_div(m, 32 * tm); }
 
+// Wavefronts per group where a workgroup's W wavefronts each work on one group:
+// one for each group that has steps, then one at a time to the group whose
+// wavefronts have the most to do each, a step of group G counting cost[G]
+// (ties: the wider format).
+inline void share_waves(const int* steps, const int* cost, int W, int* w) {
+  for (int G = 0; G < 3; ++G) w[G] = steps[G] > 0 ? 1 : 0;
+  for (int k = w[0] + w[1] + w[2]; k < W && k > 0; ++k) {
+    int best = -1;
+    int64_t most = -1;
+    for (int G = 2; G >= 0; --G) {
+      if (w[G] == 0) continue;
+      const int64_t c = ceil_div(steps[G], w[G]) * cost[G];
+      if (c > most) {
+        most = c;
+        best = G;
+      }
+    }
+    ++w[best];
+  }
+}
+constexpr int kEvenCost[3] = {1, 1, 1};     // (decode kernel)
+constexpr int kByteCost[3] = {17, 25, 33};  // a row's step with its scales, in 4 bytes (K-splitting kernel)
+
+// ---- the decode kernel ----
+
+// Up to this many activation rows (two 16-row tiles) the decode kernel may run.
+constexpr int64_t kDirectMaxM = 32;
+
+// Weight rows and wavefronts per workgroup of the decode kernel.
+struct DirectPlan {
+  int rows, waves;
+};
+
+// One activation tile (m <= 16): a whole 32-row group per workgroup (each
+// step's loads are one contiguous 2 KB record) with four wavefronts when that
+// still gives every CU a strip, else 16-row strips with eight wavefronts.
+// Measured against the even spread below on this tile: 7.7 against 8.3 us
+// (N = 14336, E2M1), equal for E4M3.
+// More: the fewest multiple of 8 rows (at least 16, at most 64) that spreads the
+// weight rows evenly over k workgroups per CU, k as small as that allows, so
+// that every CU streams about the same number of bytes and each activation
+// fragment feeds up to four weight tiles.
+inline DirectPlan direct_plan(int64_t m, int64_t n, int cus) {
+  if (m <= 16) return ceil_div(n, 32) >= cus ? DirectPlan{32, 4} : DirectPlan{16, 8};
+  int64_t k = n / (64 * (int64_t)cus);
+  for (k = k < 1 ? 1 : k;; ++k) {
+    const int64_t r = ceil_div(ceil_div(n, k * cus), 8) * 8;
+    if (r <= 64) return DirectPlan{r < 16 ? 16 : (int)r, 8};
+  }
+}
+
+// ---- the K-splitting kernel ----
+
+// Tile shapes in 32-row units of weight and activation rows.
+struct SplitShape {
+  int tn, tm;
+};
+constexpr SplitShape kSplitShapes[] = {{1, 1}, {2, 1}, {2, 2}, {2, 3}, {2, 4}};
+constexpr int kNumSplitShapes = sizeof(kSplitShapes) / sizeof(kSplitShapes[0]);
+
+// ---- the choice: the kernel with the least estimated time ----
+//
+// Estimates in us, fitted to 4500 sizes (1 .. 8192 x 128 .. 27648 x 512 .. 28672,
+// E2M1, E3M2, E4M3 and mixed splits) on 256 CUs with the weights in rotation
+// beyond the caches, as replays of a captured graph: within 6 % (K-splitting and
+// tiled kernels) and 9 % (decode kernel) in the mean square.  With weights that
+// stay in the cache, as the rule before this one was fitted, the K-splitting
+// kernel looks up to 1.6 times faster than it is in a model.  Against every
+// kernel measured at these sizes the choice is 0.4 % slower than the best in the
+// mean; the former rule was 7 % slower, worst (us, the former choice / now, M x
+// K x N): 8192 x 128 x 14336 E2M1 212 / 66, 24 x 27648 x 4096 E2M1 21.8 / 15.1,
+// 8 x 27648 x 4096 mixed 26.6 / 16.1.
+//
+// A kernel's time is a sum over the parts that bound it at some sizes: its
+// launch, the rounds of tiles over the CUs, in each round the longest chain of
+// steps of a wavefront (latency) and the steps of the tile (its loads and
+// MFMAs), and the bytes of the operands and of the result.
+struct GemmCost {
+  double once;     // per call
+  double round;    // per round of tiles
+  double chain;    // per round and step of the longest chain
+  double step;     // per round and step of the K loop
+  double w, x, y;  // per 2^20 bytes of weight, activation and result
+};
+constexpr GemmCost kSplitCost[kNumSplitShapes] = {
+    {2.46, 0.21, 0.038, 0.0566, 0.090, 0, 0.32},  {2.51, 0.29, 0.054, 0.0602, 0.113, 0.105, 0.47},
+    {1.73, 1.74, 0, 0.1073, 0.092, 0.084, 0.23},  {1.63, 2.34, 0.158, 0.1164, 0.103, 0.138, 0.26},
+    {1.48, 3.39, 0.107, 0.1268, 0.125, 0.48, 0.16}};
+constexpr GemmCost kTiled128Cost = {4.54, 0.20, 0, 0.422, 0.062, 0, 0.245};
+constexpr GemmCost kTiled256Cost = {0, 9.22, 0, 0.583, 0.084, 0.157, 0};
+
+// The decode kernel's rounds are strips per CU, at least one, without rounding
+// up (several run on a CU at a time); with one or two activation tiles.
+struct DirectCost {
+  double once, round;
+  double chain, chain_m, chain_n;  // per round and step of the longest chain: fixed, per 16 activation rows, per 16 weight rows
+  double w, y;
+};
+constexpr DirectCost kDirectCost[2] = {{2.13, 0.30, 0.139, 0.0358, 0, 0.110, 0.11}, {0.76, 1.40, 0.239, 0, 0.020, 0.120, 2.34}};
+
+// A step's time in the estimates: E2M1 1.  E3M2 codes are 24 bytes per lane and
+// block: two loads (K-splitting kernel), three (decode kernel).
+constexpr double kStepTime[3] = {1, 27.0 / 17, 33.0 / 17}, kDirectStepTime[3] = {1, 2, 33.0 / 17};
+
+// The estimates scatter by a few percent: between near equals the decode kernel
+// (up to kDirectMaxM rows) and the tiled one are taken, whose loads are the
+// more even.
+constexpr double kSplitHandicap = 1.05;
+
+inline double longest_chain(const int* steps, const int* cost, int W, const double* time) {
+  int w[3];
+  share_waves(steps, cost, W, w);
+  double most = 0;
+  for (int G = 0; G < 3; ++G) {
+    if (!steps[G]) continue;
+    const double c = (double)ceil_div(steps[G], w[G]) * time[G];
+    most = c > most ? c : most;
+  }
+  return most;
+}
+
 inline GemmRoute gemm_route(const GemmSizes& a) {
+  constexpr double kMB = 1 << 20;
+  constexpr int64_t kMaxThreads = (int64_t)1 << 32;  // a launch has fewer
   const int64_t rn = ceil_div(a.n, 32) * 32, rm = ceil_div(a.m, 32) * 32;  // the padded rows
-  const int64_t b8 = rn * 128 * a.steps[2], bytes = rn * (64 * (int64_t)a.steps[0] + 96 * (int64_t)a.steps[1]) + b8;
-  if (a.m <= kDirectMaxM && (bytes <= kDirectMaxWeight || 2 * b8 > bytes)) return {GemmKernel::kDirect, 0};
-  const double steps = a.steps[0] + a.steps[1] * (25.0 / 17) + a.steps[2] * (33.0 / 17);
-  auto cost = [&](const SplitShape& s) {
-    const int64_t rounds = ceil_div(tile_count(a.n, a.m, s.tn, s.tm), a.cus);
-    return s.once + (double)rounds * (s.round + s.step * steps);
+  const int* S = a.steps;
+  const double row_bytes = 68.0 * S[0] + 100.0 * S[1] + 132.0 * S[2];  // with scales
+  const double w = (double)rn * row_bytes / kMB, x = (double)rm * row_bytes / kMB, y = 2.0 * (double)a.m * (double)a.n / kMB;
+  const double steps = S[0] * kStepTime[0] + S[1] * kStepTime[1] + S[2] * kStepTime[2];
+  const double chain = longest_chain(S, kByteCost, 8, kStepTime);
+  auto cost = [&](const GemmCost& c, int tn, int tm) {
+    const double rounds = (double)ceil_div(tile_count(a.n, a.m, tn, tm), a.cus);
+    return c.once + rounds * (c.round + c.chain * chain + c.step * steps) + c.w * w + c.x * x + c.y * y;
   };
-  // 256 x 256 tiles when they give every CU at least one, else 256 x 128
-  // (twice the tiles)
-  GemmRoute best = {tile_count(a.n, a.m, 8, 8) >= a.cus ? GemmKernel::kTiled256 : GemmKernel::kTiled128, 0};
-  double least = cost(kTiledCost);
+  GemmRoute best = {GemmKernel::kTiled256, 0};
+  double least = cost(kTiled256Cost, 8, 8);
+  auto offer = [&](double c, GemmRoute r, int64_t threads) {
+    if (threads < kMaxThreads && c < least) {
+      least = c;
+      best = r;
+    }
+  };
+  offer(cost(kTiled128Cost, 8, 4), {GemmKernel::kTiled128, 0}, tile_count(a.n, a.m, 8, 4) * 512);
+  if (a.m <= kDirectMaxM) {
+    const DirectPlan p = direct_plan(a.m, a.n, a.cus);
+    const DirectCost& c = kDirectCost[a.m <= 16 ? 0 : 1];
+    const int64_t strips = ceil_div(a.n, p.rows);
+    const double rounds = strips > a.cus ? (double)strips / a.cus : 1.0;
+    const double per_step = c.chain + c.chain_m * (double)a.m / 16 + c.chain_n * p.rows / 16;
+    offer(c.once + rounds * (c.round + per_step * longest_chain(S, kEvenCost, p.waves, kDirectStepTime)) + c.w * w + c.y * y,
+          {GemmKernel::kDirect, 0}, strips * 64 * p.waves);
+  }
   for (int i = 0; i < kNumSplitShapes; ++i) {
     const SplitShape& s = kSplitShapes[i];
-    if (32 * s.tn > rn || 32 * s.tm > rm || tile_count(a.n, a.m, s.tn, s.tm) > kMaxSplitTiles) continue;
-    const double c = cost(s);
-    if (c < least) {
-      least = c;
-      best = {GemmKernel::kSplit, i};
-    }
+    if (32 * s.tn > rn || 32 * s.tm > rm) continue;  // the operands have not so many rows
+    offer(kSplitHandicap * cost(kSplitCost[i], s.tn, s.tm), {GemmKernel::kSplit, i}, tile_count(a.n, a.m, s.tn, s.tm) * 512);
   }
   return best;
 }

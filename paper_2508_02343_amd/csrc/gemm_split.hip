@@ -15,13 +15,14 @@
 // fp32 partial sums are added through LDS in wavefront order and rounded to
 // bf16 once (Sec. 3.2 "GEMM kernel").
 //
-// Measured (us, 75 / 18.75 / 6.25 % split, M x K x N, operands rotated; before:
-// the decode kernel up to 64 rows, the LDS-tiled one above):
-//   32 x 4096 x 28672    16.7 -> 13.0    128 x 4096 x 6144     21.2 -> 6.9
-//   64 x 4096 x 4096      6.3 ->  4.9    512 x 4096 x 4096     21.8 -> 10.8
-//   64 x 14336 x 4096    15.0 ->  9.9    333 x 27648 x 5120   120   -> 50
-// (the last takes 15 TB/s of operands from L2 into the CUs, with 140 MB of L2
-// misses; its loads alone take two thirds of that time).  Tried: four wavefronts with
+// Measured (us, 75 / 18.75 / 6.25 % split, M x K x N, weights in rotation beyond
+// the caches; before: the decode kernel up to 64 rows, the LDS-tiled one above):
+//   32 x 4096 x 28672    18.2 -> 16.8    128 x 4096 x 6144     28.0 -> 9.2
+//   64 x 4096 x 4096      6.9 ->  6.3    512 x 4096 x 4096     27.2 -> 12.5
+//   64 x 14336 x 4096    15.3 -> 14.6    333 x 27648 x 5120   133   -> 54
+// (the last takes 14 TB/s of operands from L2 into the CUs, with 140 MB of L2
+// misses; its loads alone take two thirds of that time).  Tried, with the
+// weights in the cache: four wavefronts with
 // every wavefront walking all groups and rings of four stages (7.6 and 50.6 us
 // on 128 x 4096 x 6144 and 333 x 27648 x 5120); a fragment's reload issued
 // between the MFMAs (equal, and spills on the widest tile); non-temporal weight
@@ -352,26 +353,6 @@ __global__ __launch_bounds__(kThreads) void gemm_split_kernel(GemmArgs a, int ti
   }
 }
 
-// Wavefronts per group: one for each group that has steps, then one at a time
-// to the group whose wavefronts have the most bytes each (ties: the wider
-// format).  A step is 68, 100 or 132 bytes per row with its scales.
-static void split_waves(const int* S, int* w) {
-  const int cost[3] = {17, 25, 33};
-  for (int G = 0; G < 3; ++G) w[G] = S[G] > 0 ? 1 : 0;
-  for (int k = w[0] + w[1] + w[2]; k < kWaves && k > 0; ++k) {
-    int best = -1, most = -1;
-    for (int G = 2; G >= 0; --G) {
-      if (w[G] == 0) continue;
-      const int c = (S[G] + w[G] - 1) / w[G] * cost[G];
-      if (c > most) {
-        most = c;
-        best = G;
-      }
-    }
-    ++w[best];
-  }
-}
-
 template <int TN, int TM, int FS>
 static hipError_t launch_split_fs(const GemmArgs& a, hipStream_t stream) {
   constexpr int lds = lds_bytes<TN, TM>();
@@ -384,7 +365,7 @@ static hipError_t launch_split_fs(const GemmArgs& a, hipStream_t stream) {
   }
   const int64_t tn = (a.w.rows + 32 * TN - 1) / (32 * TN), tm = (a.x.rows + 32 * TM - 1) / (32 * TM);
   int w[3];
-  split_waves(a.steps, w);
+  share_waves(a.steps, kByteCost, kWaves, w);
   hipLaunchKernelGGL((gemm_split_kernel<TN, TM, FS>), dim3((unsigned)(tn * tm)), dim3(kThreads), lds, stream, a, (int)tn,
                      (int)tm, w[0], w[1], w[2]);
   return hipGetLastError();
