@@ -49,8 +49,8 @@ constexpr int kByteCost[3] = {17, 25, 33};  // a row's step with its scales, in 
 
 // ---- the decode kernel ----
 
-// Up to this many activation rows (two 16-row tiles) the decode kernel may run.
-constexpr int64_t kDirectMaxM = 32;
+// Up to this many activation rows (four 16-row tiles) the decode kernel may run.
+constexpr int64_t kDirectMaxM = 64;
 
 // Weight rows and wavefronts per workgroup of the decode kernel.
 struct DirectPlan {
@@ -116,13 +116,14 @@ constexpr GemmCost kTiled128Cost = {4.54, 0.20, 0, 0.422, 0.062, 0, 0.245};
 constexpr GemmCost kTiled256Cost = {0, 9.22, 0, 0.583, 0.084, 0.157, 0};
 
 // The decode kernel's rounds are strips per CU, at least one, without rounding
-// up (several run on a CU at a time); with one or two activation tiles.
+// up (several run on a CU at a time); with one, two or four activation tiles.
 struct DirectCost {
   double once, round;
   double chain, chain_m, chain_n;  // per round and step of the longest chain: fixed, per 16 activation rows, per 16 weight rows
   double w, y;
 };
-constexpr DirectCost kDirectCost[2] = {{2.13, 0.30, 0.139, 0.0358, 0, 0.110, 0.11}, {0.76, 1.40, 0.239, 0, 0.020, 0.120, 2.34}};
+constexpr DirectCost kDirectCost[3] = {
+    {2.13, 0.30, 0.139, 0.0358, 0, 0.110, 0.11}, {0.76, 1.40, 0.239, 0, 0.020, 0.120, 2.34}, {0, 2.73, 0.019, 0.0965, 0.110, 0.063, 1.66}};
 
 // A step's time in the estimates: E2M1 1.  E3M2 codes are 24 bytes per lane and
 // block: two loads (K-splitting kernel), three (decode kernel).
@@ -169,7 +170,7 @@ inline GemmRoute gemm_route(const GemmSizes& a) {
   offer(cost(kTiled128Cost, 8, 4), {GemmKernel::kTiled128, 0}, tile_count(a.n, a.m, 8, 4) * 512);
   if (a.m <= kDirectMaxM) {
     const DirectPlan p = direct_plan(a.m, a.n, a.cus);
-    const DirectCost& c = kDirectCost[a.m <= 16 ? 0 : 1];
+    const DirectCost& c = kDirectCost[a.m <= 16 ? 0 : (a.m <= 32 ? 1 : 2)];
     const int64_t strips = ceil_div(a.n, p.rows);
     const double rounds = strips > a.cus ? (double)strips / a.cus : 1.0;
     const double per_step = c.chain + c.chain_m * (double)a.m / 16 + c.chain_n * p.rows / 16;

@@ -1,7 +1,7 @@
 // Mixed MX GEMM for the shapes between decode and prefill (batched decode,
-// prompt chunks, few weight rows): too many activation rows for the decode
-// kernel's one or two 16-row tiles, too few output tiles for the LDS-tiled kernel to give
-// every CU one.
+// prompt chunks, few weight rows): too many activation rows, or too few steps
+// for its weight rows, for the decode kernel, too few output tiles for the
+// LDS-tiled kernel to give every CU one.
 //
 // What bounds these shapes is how many CUs share the operand stream, and the
 // latency and rate at which one CU takes it, so a workgroup covers a small

@@ -99,7 +99,7 @@ hipError_t launch_calibrate(const CalibArgs& a, hipStream_t stream);
 // with hipGetSymbolAddress on the first call on each device, with that
 // device current, and cached per device.  Allocates nothing.
 hipError_t calibrate_scratch(void** ptr);
-hipError_t launch_gemm_direct(const GemmArgs& a, hipStream_t stream);  // at most 32 activation rows
+hipError_t launch_gemm_direct(const GemmArgs& a, hipStream_t stream);  // at most 64 activation rows
 hipError_t launch_gemm_tiled(const GemmArgs& a, bool square, hipStream_t stream);  // 256 x 256 tiles, else 256 x 128
 // The K-splitting kernel with a tile shape (an index into kSplitShapes) whose
 // rows the padded operands have.

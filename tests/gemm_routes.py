@@ -28,7 +28,8 @@ int main() {
       tn = mm::kSplitShapes[r.shape].tn;
       tm = mm::kSplitShapes[r.shape].tm;
     }
-    printf("%%s %%dx%%d %%lld\\n", name, 32 * tn, 32 * tm, (long long)mm::tile_count(n, m, tn, tm));
+    const mm::DirectPlan p = r.kernel == mm::GemmKernel::kDirect ? mm::direct_plan(m, n, z.cus) : mm::DirectPlan{0, 0};
+    printf("%%s %%dx%%d %%lld %%d\\n", name, 32 * tn, 32 * tm, (long long)mm::tile_count(n, m, tn, tm), p.rows);
   }
 }
 """
@@ -45,10 +46,22 @@ def _program() -> str:
 
 
 @functools.lru_cache(maxsize=None)
+def _run(M: int, N: int, split, cus: int) -> list[str]:
+    steps = [-(-(p // 32) // 4) for p in split]
+    line = " ".join(str(v) for v in (M, N, *steps, cus))
+    return subprocess.run([_program()], input=line, check=True, capture_output=True, text=True).stdout.split()
+
+
 def route(M: int, N: int, split, cus: int = 256) -> tuple[str, int]:
     """("direct" | "split 64x32" | "tiled 256x128" ..., tiles) of an [M, K] x [N, K]
     product with this split (tiles without a meaning for "direct")."""
-    steps = [-(-(p // 32) // 4) for p in split]
-    line = " ".join(str(v) for v in (M, N, *steps, cus))
-    out = subprocess.run([_program()], input=line, check=True, capture_output=True, text=True).stdout.split()
+    out = _run(M, N, tuple(split), cus)
     return out[0] if out[0] == "direct" else f"{out[0]} {out[1]}", int(out[2])
+
+
+def kernel(M: int, N: int, split, cus: int = 256) -> str:
+    """The compiled kernel such a product takes: as route(), the decode kernel with
+    its activation tiles and the weight rows of a strip ("direct 2 tiles 24 rows")."""
+    name, _ = route(M, N, split, cus)
+    tiles = 1 if M <= 16 else (2 if M <= 32 else 4)
+    return f"direct {tiles} tiles {_run(M, N, tuple(split), cus)[3]} rows" if name == "direct" else name

@@ -4,7 +4,8 @@ same helper."""
 
 import pytest
 
-from tests.gemm_routes import route
+from tests.gemm_cases import CASES
+from tests.gemm_routes import kernel, route
 
 
 @pytest.mark.parametrize("M,N", [((1 << 31) - 1, 8), ((1 << 31) - 1, 64), (1 << 28, 32), ((1 << 28) - 31, 33),
@@ -34,6 +35,13 @@ MEASURED = [
     (1, 4096, (0, 14336, 0), {D: 11.1, S1: 18.2, S2: 24.0}),
     # two activation tiles against many weight rows of few channels
     (32, 28672, (1024, 0, 0), {D: 8.4, S1: 7.2, S2: 6.7, T1: 9.3}),
+    # four activation tiles: 8-bit codes and long K on the decode kernel
+    (40, 10240, (0, 0, 14336), {D: 30.6, S1: 50.8, S2: 52.8, S3: 40.8, T1: 91.6}),
+    (40, 6144, (0, 0, 8192), {D: 13.9, S1: 21.4, S2: 18.4, S3: 23.6, T1: 54.6}),
+    (64, 6144, (0, 0, 4096), {D: 9.9, S1: 12.2, S2: 11.0, S3: 13.8, T1: 30.2}),
+    (33, 6144, _mix(14336), {D: 16.7, S1: 23.7, S2: 19.3, S3: 24.3, T1: 56.4}),
+    (64, 1024, (0, 14336, 0), {D: 19.3, S1: 14.7, S2: 20.9, S3: 28.0, T1: 76.4}),
+    (64, 28672, _mix(4096), {D: 22.4, S1: 25.3, S2: 22.6, S3: 20.3, T1: 23.3}),
     # few steps at prefill sizes: a K-splitting tile would mostly add up zeros
     (8192, 14336, (128, 0, 0), {S2: 212, S3: 232, S4: 232, S5: 218, T1: 62.2, T2: 65.7}),
     (2048, 28672, (256, 0, 0), {S2: 126, S3: 135, S4: 127, S5: 115, T1: 41.9, T2: 41.0}),
@@ -54,3 +62,8 @@ def test_choice_is_near_the_fastest_measured(M, N, split, times):
     """Within 8 % of the fastest (the estimates scatter by 5 to 9 %)."""
     name, _ = route(M, N, split)
     assert times[name] <= 1.08 * min(times.values()), (name, times)
+
+
+@pytest.mark.parametrize("name,M,N,split", CASES, ids=str)
+def test_cases_reach_the_kernel_that_they_name(name, M, N, split):
+    assert kernel(M, N, split) == name

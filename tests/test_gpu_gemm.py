@@ -12,6 +12,7 @@ import torch
 
 from oracle import mx_oracle as O
 from paper_2508_02343_amd import workloads as W
+from tests.gemm_cases import CASES
 from tests.gpu_helpers import assert_codes_equal, assert_gemm_close, note, to_dev_bf16, to_dev_perm, y_to_f64
 
 pytestmark = pytest.mark.gpu
@@ -268,6 +269,31 @@ def test_alternative_formats(M, N, formats):
     assert_codes_equal(a, ra, ctx=ctx + " A")
     assert_codes_equal(w, rw, ctx=ctx + " W")
     assert_gemm_close(y_to_f64(y), O.gemm_mixed(ra, rw), ctx=ctx)
+
+
+@pytest.mark.parametrize("formats", [("E3M2", "E4M3"), ("E2M3", "E4M3"), ("E3M2", "E5M2"), ("E2M3", "E5M2")], ids="-".join)
+@pytest.mark.parametrize("name,M,N,split", CASES, ids=str)
+def test_every_kernel(name, M, N, split, formats):
+    """Every compiled kernel with every format set: the first and last 70 rows and
+    columns and 60 others against the oracle."""
+    note(f"{name} {formats} M={M} N={N} split={split}")
+    xb, wb, perm = _rand_case(M, N, split, seed=M + N + split[2])
+    b = _b()
+    p = to_dev_perm(perm)
+    a = b.quantize_act(to_dev_bf16(xb), p, split, formats=formats)
+    w = b.quantize_weight(to_dev_bf16(wb), p, split, formats=formats)
+    y = b.gemm(a, w)
+    torch.cuda.synchronize()
+
+    def some(n):
+        return np.unique(np.clip(np.concatenate([np.arange(70), n - 1 - np.arange(70),
+                                                 np.random.default_rng(n).choice(n, 60)]), 0, n - 1))
+
+    rows, cols = some(M), some(N)
+    fm = (O.E2M1, O.FORMATS[formats[0]], O.FORMATS[formats[1]])
+    ra, rw = O.quantize_mixed(xb[rows], perm, split, fm), O.quantize_mixed(wb[cols], perm, split, fm)
+    got = y_to_f64(y[torch.from_numpy(rows).cuda()])[:, cols]
+    assert_gemm_close(got, O.gemm_mixed(ra, rw), ctx=f"{name} {formats}")
 
 
 def test_mixed_formats_are_rejected():
