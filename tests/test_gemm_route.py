@@ -4,7 +4,7 @@ same helper."""
 
 import pytest
 
-from tests.gemm_cases import CASES
+from tests.gemm_cases import CASES, FEW_STAGES
 from tests.gemm_routes import kernel, route
 
 
@@ -67,3 +67,8 @@ def test_choice_is_near_the_fastest_measured(M, N, split, times):
 @pytest.mark.parametrize("name,M,N,split", CASES, ids=str)
 def test_cases_reach_the_kernel_that_they_name(name, M, N, split):
     assert kernel(M, N, split) == name
+
+
+@pytest.mark.parametrize("M,N,split", FEW_STAGES, ids=str)
+def test_few_stages_reach_the_tiled_kernel(M, N, split):
+    assert kernel(M, N, split) == ("tiled 256x256" if (M, N, split) in FEW_STAGES[-2:] else "tiled 256x128")

@@ -12,7 +12,7 @@ import torch
 
 from oracle import mx_oracle as O
 from paper_2508_02343_amd import workloads as W
-from tests.gemm_cases import CASES
+from tests.gemm_cases import CASES, FEW_STAGES
 from tests.gpu_helpers import assert_codes_equal, assert_gemm_close, note, to_dev_bf16, to_dev_perm, y_to_f64
 
 pytestmark = pytest.mark.gpu
@@ -70,14 +70,12 @@ def test_ragged(M, N, split):
 
 
 @pytest.mark.parametrize("formats", [("E3M2", "E4M3"), ("E2M3", "E5M2")], ids="-".join)
-@pytest.mark.parametrize("M,N,split", [(1990, 4050, (32, 0, 0)), (2000, 4040, (0, 0, 96)), (1921, 3841, (160, 32, 64)),
-                                       (2040, 4090, (640, 96, 160)), (1985, 4089, (1152, 0, 0)),
-                                       (4000, 4090, (32, 0, 32)), (3841, 4001, (640, 224, 96))], ids=str)
+@pytest.mark.parametrize("M,N,split", FEW_STAGES, ids=str)
 def test_tiled_few_stages(M, N, split, formats):
     """The LDS-tiled kernel's ring with fewer stages than slots, as many and a
     few more, groups of one stage and groups that change while the ring fills:
-    256 x 128 tiles (loads by producer wavefronts) and, from one 256 x 256 tile
-    per CU, those."""
+    256 x 128 tiles (loads by producer wavefronts) and, in the last two, 256 x 256
+    tiles."""
     note(f"tiled M={M} N={N} split={split} {formats}")
     xb, wb, perm = _rand_case(M, N, split, seed=M + N + split[0])
     b = _b()
@@ -96,12 +94,10 @@ def test_tiled_few_stages(M, N, split, formats):
                                        (20, 12000, (96, 160, 96)), (50, 12000, (256, 128, 128)),
                                        (8, 20008, (256, 128, 128)), (64, 20000, (0, 0, 512))])
 def test_decode_strips(M, N, split):
-    """Decode kernel (M <= 64) at the strip widths its launch picks: for one
-    activation tile 16-row strips (N = 6001) or whole 32-row groups
-    (N = 12000, 20008: a part-filled last group); for two or four activation
-    tiles rows per workgroup that are not a multiple of 16 (24, 48 and 40 on
-    256 CUs: part-filled last tiles, two or four tiles per workgroup), the
-    last at a width that needs two workgroups per CU."""
+    """At most 64 rows against weights of few channels: the decode kernel's 16-row
+    strips (N = 6001) and whole 32-row groups (N = 12000, 20008: a part-filled last
+    group) with one activation tile, and the K-splitting kernel's narrow tiles
+    above 16 rows, with part-filled last tiles."""
     note(f"decode strips M={M} N={N} split={split}")
     xb, wb, perm = _rand_case(M, N, split, seed=M * 11 + N + split[0])
     _check_full(xb, wb, perm, split, f"M{M} N{N} {split}")
@@ -121,9 +117,9 @@ def test_decode_long_k(M, N):
 @pytest.mark.parametrize("split", [(96, 160, 96), (352, 0, 0), (0, 352, 0), (0, 0, 352), (128, 0, 224)])
 @pytest.mark.parametrize("M,N", [(3000, 5400), (1000, 1000)])
 def test_ragged_large(M, N, split):
-    """Every output of shapes whose tile grids run the 256 x 256 tiles
-    (12 x 22 tiles, at least one per CU) and the 256 x 128 tiles (4 x 8),
-    both with ragged last tiles in M and N."""
+    """Every output of shapes of the LDS-tiled kernel (24 x 22 tiles of 256 x 128)
+    and of the K-splitting one (16 x 16 tiles of 64 x 64), both with ragged last
+    tiles in M and N."""
     note(f"ragged large M={M} N={N} split={split}")
     xb, wb, perm = _rand_case(M, N, split, seed=M + N + split[1])
     _check_full(xb, wb, perm, split, f"M{M} N{N} {split}")
@@ -187,11 +183,12 @@ def test_prefill_configs_sampled(w):
 @pytest.mark.parametrize("M,N", [(17, 33), (32, 4100), (20, 9000), (33, 31), (65, 1003), (129, 2050), (192, 5500),
                                  (250, 4097)])
 def test_split_k_tiles(M, N, split):
-    """The K-splitting kernel between the decode and the tiled one: its tile
-    shapes (32 or 64 weight rows by 32 to 128 activation rows, chosen by size),
-    last tiles that reach back into the tile before in both directions,
+    """Sizes between the decode and the tiled kernel: above 64 rows the K-splitting
+    kernel's tile shapes (32 or 64 weight rows by 32 to 96 activation rows), last
+    tiles that reach back into the tile before in both directions,
     columns that are no multiple of 8, wavefronts without steps, with one and
-    with an odd number of steps.  Every output against the oracle."""
+    with an odd number of steps; below, the decode kernel's strips at the same
+    sizes.  Every output against the oracle."""
     note(f"split-K M={M} N={N} split={split}")
     xb, wb, perm = _rand_case(M, N, split, seed=M + 3 * N + split[0])
     _check_full(xb, wb, perm, split, f"M{M} N{N} {split}")
@@ -202,8 +199,7 @@ def test_split_k_tiles(M, N, split):
                                        (9, 9000, (5120, 1024, 512))], ids=str)
 def test_split_k_long(M, N, split, formats):
     """The same with many steps per wavefront: the widest tile (64 x 128 at 500
-    rows), odd step counts, and the decode kernel's side of its 40 MB line (9000
-    rows of 6656 channels: 35 MB)."""
+    rows), odd step counts; and the decode kernel with 9 rows."""
     note(f"split-K long M={M} N={N} split={split} {formats}")
     xb, wb, perm = _rand_case(M, N, split, seed=M + N)
     b = _b()
@@ -219,8 +215,8 @@ def test_split_k_long(M, N, split, formats):
 
 @pytest.mark.parametrize("M", [1, 16])
 def test_split_k_decode(M):
-    """At most 16 rows against a weight of more than 40 MB that is not mostly
-    8-bit: the K-splitting kernel (256 sampled columns against the oracle)."""
+    """At most 16 rows against a weight of 48 MB (256 sampled columns against the
+    oracle)."""
     N, split = 20000, (3072, 768, 256)
     note(f"split-K decode M={M}")
     xb, wb, perm = _rand_case(M, N, split, seed=M)
@@ -252,8 +248,8 @@ def test_one_activation_feeds_two_weights():
 @pytest.mark.parametrize("formats", [("E2M3", "E5M2"), ("E2M3", "E4M3"), ("E3M2", "E5M2")], ids="-".join)
 @pytest.mark.parametrize("M,N", [(5, 70), (37, 130), (300, 260)])
 def test_alternative_formats(M, N, formats):
-    """The ablation's MXFP6 = E2M3 and MXFP8 = E5M2 variants through both
-    GEMM kernels (decode for M <= 64, tiled above)."""
+    """The ablation's MXFP6 = E2M3 and MXFP8 = E5M2 variants through the decode
+    and the K-splitting kernel (every kernel: test_every_kernel)."""
     split = (96, 160, 96)
     note(f"formats {formats} M={M} N={N}")
     xb, wb, perm = _rand_case(M, N, split, seed=M * 11 + N)
