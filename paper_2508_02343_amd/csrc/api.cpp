@@ -205,6 +205,14 @@ hipError_t device_cus(int* cus) {
   return hipSuccess;
 }
 
+hipError_t allow_lds(DeviceOnce& once, const void* kernel, int bytes) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  return (hipError_t)once.run(
+      dev, [&] { return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
+
 }  // namespace mm
 
 extern "C" {

@@ -356,13 +356,9 @@ __global__ __launch_bounds__(kThreads) void gemm_split_kernel(GemmArgs a, int ti
 template <int TN, int TM, int FS>
 static hipError_t launch_split_fs(const GemmArgs& a, hipStream_t stream) {
   constexpr int lds = lds_bytes<TN, TM>();
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_split_kernel<TN, TM, FS>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static DeviceOnce once;
+  hipError_t e = allow_lds(once, reinterpret_cast<const void*>(gemm_split_kernel<TN, TM, FS>), lds);
+  if (e != hipSuccess) return e;
   const int64_t tn = (a.w.rows + 32 * TN - 1) / (32 * TN), tm = (a.x.rows + 32 * TM - 1) / (32 * TM);
   int w[3];
   share_waves(a.steps, kByteCost, kWaves, w);

@@ -772,13 +772,9 @@ __global__ __launch_bounds__((Tile<BN, BM>::kThreads), 1) void gemm_tiled_kernel
 
 template <int BN, int BM, int FS>
 static hipError_t launch_tile_fs(const GemmArgs& a, hipStream_t stream) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tiled_kernel<BN, BM, FS>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static DeviceOnce once;
+  hipError_t e = allow_lds(once, reinterpret_cast<const void*>(gemm_tiled_kernel<BN, BM, FS>), kLdsBytes);
+  if (e != hipSuccess) return e;
   const int tn = (int)((a.w.rows + BN - 1) / BN), tm = (int)((a.x.rows + BM - 1) / BM);
   hipLaunchKernelGGL((gemm_tiled_kernel<BN, BM, FS>), dim3((unsigned)(tn * tm)), dim3(Tile<BN, BM>::kThreads), kLdsBytes, stream, a,
                      tn, tm);

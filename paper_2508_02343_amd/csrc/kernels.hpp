@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "device_once.hpp"
+
 namespace mm {
 
 // Packed-layout constants (the layout is documented in include/micromix.h).
@@ -106,5 +108,8 @@ hipError_t launch_gemm_tiled(const GemmArgs& a, bool square, hipStream_t stream)
 hipError_t launch_gemm_split(const GemmArgs& a, int shape, hipStream_t stream);
 // CUs of the current device (cached per thread for the last device).
 hipError_t device_cus(int* cus);
+// Lets a kernel have this much dynamic LDS on the current device (`once`: the
+// kernel's own).
+hipError_t allow_lds(DeviceOnce& once, const void* kernel, int bytes);
 
 }  // namespace mm

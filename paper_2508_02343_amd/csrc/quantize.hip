@@ -505,16 +505,12 @@ __global__ __launch_bounds__(kMaxThreads) void quantize_kernel(QuantArgs a) {
 
 template <int RH, bool kNorm>
 static hipError_t launch_rows(const QuantArgs& a, hipStream_t stream) {
-  static bool attr = false;
+  static DeviceOnce once;
   constexpr int kLds = 160 * 1024;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(quantize_kernel<RH, kNorm>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  hipError_t e = allow_lds(once, reinterpret_cast<const void*>(quantize_kernel<RH, kNorm>), kLds);
+  if (e != hipSuccess) return e;
   int cus = 0;
-  hipError_t e = device_cus(&cus);
+  e = device_cus(&cus);
   if (e != hipSuccess) return e;
   const int waves = (RH * (a.K >> 5) + 63) / 64;
   const size_t lds = (size_t)RH * (2 * a.K + 16) + (kNorm ? 2 * (size_t)a.K + 8 * (kMaxThreads / 64) * RH : 0);
