@@ -519,9 +519,13 @@ static hipError_t launch_rows(const QuantArgs& a, hipStream_t stream) {
   const int waves = (RH * (a.K >> 5) + 63) / 64;
   const size_t lds = (size_t)RH * (2 * a.K + 16) + (kNorm ? 2 * (size_t)a.K + 8 * (kMaxThreads / 64) * RH : 0);
   if (64 * waves > kMaxThreads || lds > kLds) return hipErrorInvalidValue;  // cannot happen: see launch_quantize
-  // as many workgroups as the chip holds at once (16 wavefronts and 160 KB of
-  // LDS per CU), so that each keeps its sigma for all of its passes
-  int64_t per = 16 / waves;
+  // as many workgroups as the chip holds at once (four wavefronts on each of a
+  // CU's four SIMDs and 160 KB of LDS), so that each keeps its sigma for all of its
+  // passes.  The wavefronts of a workgroup spread over the SIMDs evenly: of five,
+  // two share one, and a third such workgroup finds no room (counted in, those
+  // left over ran behind the others: 3144 x 5120 16.6 -> 13.2, with the norm 27.9 ->
+  // 20.8; 28557 x 2272 48.8 -> 39.3 us).
+  int64_t per = waves <= 4 ? 16 / waves : 4 / ((waves + 3) / 4);
   if (per * lds > kLds) per = kLds / lds;
   const int64_t passes = (a.rp + RH - 1) / RH, cap = per * cus;
   hipLaunchKernelGGL((quantize_kernel<RH, kNorm>), dim3((unsigned)(passes < cap ? passes : cap)), dim3(64 * waves), lds,
@@ -534,18 +538,31 @@ static hipError_t launch_rows(const QuantArgs& a, hipStream_t stream) {
 // and smaller workgroups, which start and finish sooner, and win where there is
 // little to stream.  Measured (us, 1 / 2 / 4 rows per pass): 128 x 4096 3.6 / 3.7
 // / 4.3, 512 x 4096 4.7 / 4.5 / 5.0, 2048 x 4096 10.3 / 8.1 / 8.6, 4096 x 4096
-// 15.5 / 12.7 / 13.1, 14336 x 4096 42.6 / 35.1 / 33.0, 8192 x 5120 33 / 30.4 /
-// 25.0, with the norm 512 x 4096 7.6 / 6.5 / 8.0 and 8192 x 5120 43 / 48 / 41;
+// 15.4 / 12.8 / 13.4, 14336 x 4096 42.6 / 35.1 / 33.0, 8192 x 5120 34 / 26.3 /
+// 26.1, with the norm 512 x 4096 7.6 / 6.5 / 8.0 and 4096 x 5120 25.2 / 24.7 / 24.9;
 // below 2048 channels four rows are never slower (1000 x 608: 4.0 / 3.9 / 3.6),
 // and up to 512 sixteen beat them without the norm (28672 x 512: 12.2 / 10.8).
+// Above 8192 channels one row, as long as every row is in flight at once (256 x
+// 14336 6.9 / 7.7, 384 x 14336 9.1 / 8.1).
+// With the norm, whose arithmetic bounds the large sizes, four rows per pass can
+// leave the CU with too few wavefronts: two workgroups of five (K 2080 .. 2560:
+// two rows make five of three, 28557 x 2560 67.1 -> 65.3) or one of nine or ten
+// (K 4128 .. 5120: one row makes five of three, 28557 x 5120 125 -> 118, 8192 x
+// 5120 42.3 -> 40.9, but only from 4480 channels on, which fill most of their
+// lanes: 28557 x 4160 112 -> 121).
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream) {
   if (a.rows == 0) return hipSuccess;
   const bool norm = a.norm != 0;
   const int64_t n = a.rp * a.K;
   int rh = a.K <= 8192 ? 4 : (a.K <= 16384 ? 2 : 1);
   if (a.K >= 2048) {
-    if (n < (1 << 20)) rh = 1;
+    int cus = 0;
+    hipError_t e = device_cus(&cus);
+    if (e != hipSuccess) return e;
+    if (n < (1 << 20) || (a.K > 8192 && a.rp <= cus)) rh = 1;
     else if (n < (24 << 20) && rh > 2) rh = 2;
+    else if (norm && a.K > 2048 && a.K <= 2560) rh = 2;
+    else if (norm && a.K >= 4480 && a.K <= 5120) rh = 1;
   } else if (a.K <= 512 && !norm) {
     rh = 16;
   }

@@ -116,7 +116,7 @@ RAGGED = [(96, 160, 96), (352, 0, 0), (0, 352, 0), (0, 0, 352), (32, 32, 288)]
 
 
 @pytest.mark.parametrize("rows,K", [(70, 512), (35, 2016), (33, 2048), (520, 2080), (3, 8192), (140, 8192),
-                                    (3, 8224), (70, 15360), (33, 16416), (2, 32768)])
+                                    (3, 8224), (70, 15360), (259, 9600), (33, 16416), (2, 32768)])
 def test_rows_per_pass(rows, K):
     """1, 2 or 4 rows per pass by channels and values (the square sums of a
     row come from all or some of the workgroup's wavefronts, up to sixteen)."""
@@ -127,6 +127,23 @@ def test_rows_per_pass(rows, K):
     g = (1.0 + 0.25 * rng.standard_normal(K)).astype(np.float32)
     _check(W.f32_to_bf16_bits(x), W.f32_to_bf16_bits(g), 1e-5, rng.permutation(K).astype(np.int32),
            (p4, p6, K - p4 - p6), ctx="rows per pass", ld_extra=8)
+
+
+@pytest.mark.parametrize("rows,K", [(10300, 2528), (5700, 4512), (6300, 4192)])
+def test_rows_per_pass_large(rows, K):
+    """Two, one and four rows per pass where there is much to stream (sampled rows)."""
+    rng = np.random.default_rng(rows + K)
+    xb = W.f32_to_bf16_bits(rng.standard_normal((rows, K), dtype=np.float32))
+    gb, perm = _gamma(K, K), rng.permutation(K).astype(np.int32)
+    p4, p6 = K // 2 // 32 * 32, K // 4 // 32 * 32
+    split = (p4, p6, K - p4 - p6)
+    note(f"rmsnorm+quantize large rows={rows} K={K}")
+    out = _run(xb, gb, 1e-5, perm, split)
+    some = np.unique(np.concatenate([np.arange(9), rows - 1 - np.arange(9), rng.integers(0, rows, 60)]))
+    r32, _, amb = _factors(xb[some], 1e-5)
+    assert not amb.any()
+    ref = O.quantize_mixed(O.rmsnorm_apply(xb[some], gb, r32), perm, split)
+    assert_codes_equal(out, ref, rows=some, ctx=f"{rows}x{K}")
 
 
 @pytest.mark.parametrize("split", RAGGED)

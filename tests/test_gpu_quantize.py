@@ -47,13 +47,13 @@ RAGGED_SPLITS = [(96, 160, 96), (352, 0, 0), (0, 352, 0), (0, 0, 352), (32, 32, 
 
 
 @pytest.mark.parametrize("rows,K", [(70, 512), (1, 32), (515, 64), (70, 544), (90, 2016), (33, 2048), (500, 2080),
-                                    (3, 8192), (140, 8192), (3010, 8192), (3, 8224), (65, 16384), (33, 16416),
-                                    (2, 32768)])
+                                    (3, 8192), (140, 8192), (3010, 8192), (3, 8224), (250, 8224), (259, 8224),
+                                    (3, 16384), (65, 16384), (33, 16416), (2, 32768)])
 def test_rows_per_pass(rows, K):
     """The sizes at which the kernel changes its rows per pass (16 up to 512
-    channels, 4 below 2048, then 1, 2 or 4 by the number of values, at most 2
-    above 8192 and 1 above 16384 channels), with last passes of padding rows
-    only.  Large inputs are compared on sampled rows."""
+    channels, 4 below 2048, then 1, 2 or 4 by the number of values, above 8192
+    channels 1 up to 256 rows and then 2, 1 above 16384), with last passes of
+    padding rows only.  Large inputs are compared on sampled rows."""
     p4, p6 = K // 2 // 32 * 32, K // 4 // 32 * 32
     split = (p4, p6, K - p4 - p6)
     note(f"rows per pass rows={rows} K={K}")
