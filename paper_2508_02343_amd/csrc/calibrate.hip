@@ -14,10 +14,10 @@
 //      and one fixed chunk of rows (HBM-bound, 2 bytes read per element) and
 //      writes its partial sums and its largest |x|.  About one workgroup per
 //      CU streams best: more concurrent row streams lose DRAM locality;
-//   2. means: each channel adds its chunk partials in a fixed order, / L.  Up
-//      to kFuseK channels the rank workgroups do this for the channels that
-//      they compare, again in each workgroup, which is less than a launch of
-//      its own and the wait for it;
+//   2. means: each channel adds its chunk partials in a fixed order, / L.  At
+//      most sizes (see kFuseK) the rank workgroups do this for the channels that
+//      they compare, again in each workgroup, which is less than a launch of its
+//      own and the wait for it;
 //   3. rank: workgroup (jb, sl) compares 256 channels with a 256-channel
 //      slice of the means and stores, per channel, how many of them sort
 //      before it under the strict order (mean, index); the workgroups of
@@ -28,8 +28,7 @@
 // Measured, whole call (us, separate means -> fused): 32768 x 4096 59.2 -> 54.7
 // (column sums 41.5), 2048 x 4096 22.2 -> 18.8, 300 x 1024 21.8 -> 16.4, 32768 x
 // 5120 73.3 -> 71.6, but 16384 x 14336 106 -> 120 and 2000 x 32768 114 -> 195
-// (every mean formed K / 256 times), so above kFuseK channels the means stay
-// a launch of their own.
+// (every mean formed K / 256 times).
 // No atomics: every result is written by exactly one thread.
 #include <mutex>
 
@@ -51,7 +50,13 @@ constexpr int kLaneCols = 8;               // channels per lane (one 16-byte loa
 constexpr int kTileCols = 64 * kLaneCols;  // channels per column-sum workgroup
 constexpr int kMeanChains = 16;            // partial sums of a mean (one chunk subset each)
 constexpr int kRankThreads = 256;          // channels per rank workgroup
-constexpr int kFuseK = 8192;               // channels up to which the rank kernel forms the means
+// Where the rank kernel forms the means: up to kFuseK channels, or up to kFuseFewK
+// with at most kFuseFew row chunks (us, separate / fused: 1461 x 5696 26.9 / 27.4,
+// 2046 x 6720 29.1 / 31.0, 1024 x 8192 25.3 / 29.6, but 601 x 5568 25.4 / 22.3, 716 x
+// 6208 27.7 / 26.1, 83 x 7264 25.7 / 23.5); not at up to kSlowK channels with more
+// than three chunks per chain, whose few threads would add them one after the
+// other (9314 x 32 15.4 / 17.2, 7507 x 64 15.1 / 16.1; 7250 x 128 16.2 / 15.1).
+constexpr int kFuseK = 5632, kFuseFewK = 7680, kFuseFew = 12, kSlowK = 64;
 constexpr int kRankSlice = kCalibSlice;    // means compared per rank workgroup
 constexpr uint32_t kF32Inf = 0x7F800000u;  // |x| fp32 patterns at or above this are Inf or NaN
 
@@ -186,9 +191,18 @@ __global__ __launch_bounds__(64 * kSumWaves) void colsum_kernel(CalibArgs a) {
   for (int i = 0; i < kLaneCols / 2; ++i) out[i] = make_double2(s[2 * i], s[2 * i + 1]);
 }
 
-__global__ __launch_bounds__(kRankThreads) void mean_kernel(CalibArgs a) {
-  const int j = blockIdx.x * kRankThreads + threadIdx.x;
-  if (j < a.K) a.mean[j] = channel_mean(a, j);
+__global__ __launch_bounds__(64 * kMeanChains) void mean_kernel(CalibArgs a) {
+  __shared__ double red[kMeanChains][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;  // a wavefront per chain
+  const int j = blockIdx.x * 64 + lane;
+  double s = 0.0;
+  if (j < a.K)
+    for (int c = wave; c < a.nchunks; c += kMeanChains) s += a.partial[(int64_t)c * a.K + j];
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || j >= a.K) return;
+  for (int w = 1; w < kMeanChains; ++w) s += red[w][lane];
+  a.mean[j] = s / (double)a.rows;
 }
 
 // kParts: threads per channel, each comparing with its part of the slice (the
@@ -306,10 +320,11 @@ hipError_t launch_calibrate(const CalibArgs& a, hipStream_t stream) {
   const int tiles = (a.K + kTileCols - 1) / kTileCols;
   hipLaunchKernelGGL(colsum_kernel, dim3(tiles, a.nchunks), dim3(64 * kSumWaves), 0, stream, a);
   const dim3 ranks((a.K + kRankThreads - 1) / kRankThreads, (a.K + kRankSlice - 1) / kRankSlice);
-  if (a.K <= kFuseK) {
+  const bool slow = a.K <= kSlowK && a.nchunks > 3 * kMeanChains;
+  if (!slow && a.K <= (a.nchunks <= kFuseFew ? kFuseFewK : kFuseK)) {
     hipLaunchKernelGGL((rank_kernel<4, true>), ranks, dim3(kRankThreads * 4), 0, stream, a);
   } else {
-    hipLaunchKernelGGL(mean_kernel, dim3((a.K + kRankThreads - 1) / kRankThreads), dim3(kRankThreads), 0, stream, a);
+    hipLaunchKernelGGL(mean_kernel, dim3((a.K + 63) / 64), dim3(64 * kMeanChains), 0, stream, a);
     hipLaunchKernelGGL((rank_kernel<1, false>), ranks, dim3(kRankThreads), 0, stream, a);
   }
   hipLaunchKernelGGL(place_kernel, dim3((a.K + kRankThreads - 1) / kRankThreads), dim3(kRankThreads), 0, stream, a);

@@ -86,14 +86,17 @@ def test_full_calibration_sets():
         _check(W.calibration_bits(L, K, seed), ctx=f"full{seed}")
 
 
-@pytest.mark.parametrize("L,K", [(5, 256), (1100, 288), (70, 8160), (2100, 8192), (70, 8224)])
+@pytest.mark.parametrize("L,K", [(5, 256), (1100, 288), (70, 8160), (2100, 8192), (70, 8224), (1500, 5632), (1500, 5664),
+                                 (700, 7680), (900, 7680), (70, 7712), (3000, 64), (3200, 64), (3200, 96)])
 def test_means_in_the_rank_kernel(L, K):
-    """Up to 8192 channels the rank kernel forms the means itself (1 to 128 row
-    chunks, a last slice of 32 channels), above that they are a launch of their
-    own; columns that are equal in pairs half the width apart must keep their
+    """Up to 5632 channels, or 7680 with at most 12 row chunks, the rank kernel forms
+    the means itself (1 to 128 row chunks, a last slice of 32 channels); above, and
+    at 64 channels with more than 48 chunks, they are a launch of their own;
+    columns that are equal in pairs half the width apart must keep their
     order whichever workgroups compare them."""
     bits = W.calibration_bits(L, K, L + K)
-    bits[:, K // 2:K // 2 + 40] = bits[:, :40]
+    n = min(40, K // 2)
+    bits[:, K // 2:K // 2 + n] = bits[:, :n]
     _check(bits, ctx="rank means")
 
 
