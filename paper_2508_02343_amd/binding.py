@@ -234,6 +234,10 @@ def _check_mx(t: MXTensor, rows: int, K: int, split, device, name: str) -> None:
     if t.rows != rows or t.K != K or tuple(map(int, t.split)) != split:
         raise ValueError(f"{name} is [{t.rows}, {t.K}] split {tuple(t.split)}, expected [{rows}, {K}] split "
                          f"{split}")
+    _check_buffers(t, rows, K, split, device, name)
+
+
+def _check_buffers(t: MXTensor, rows: int, K: int, split: tuple, device, name: str) -> None:
     index = -1 if device.type == "cpu" else device.index  # (comparing devices costs four times as much)
     for b, buf, need in zip(("q4", "q6", "q8", "sc"), (t.q4, t.q6, t.q8, t.sc), _buffer_sizes(rows, K, split)):
         n = 0 if buf is None else buf.nbytes
@@ -286,8 +290,8 @@ def quantize_weight(w: torch.Tensor, perm: torch.Tensor, split, out: MXTensor | 
 def gemm(a: MXTensor, w: MXTensor, y: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """mm_gemm: Y[M, N] = A W^T in bf16 (one fp32 accumulator over all groups)."""
     device = a.sc.device
-    _check_mx(a, a.rows, a.K, a.split, device, "a")
-    _check_mx(w, w.rows, w.K, w.split, device, "w")
+    _check_buffers(a, a.rows, a.K, tuple(map(int, a.split)), device, "a")
+    _check_buffers(w, w.rows, w.K, tuple(map(int, w.split)), device, "w")
     M, N = a.rows, w.rows
     if y is None:
         y = torch.empty((M, _round16(N) if N % 8 else N), dtype=torch.bfloat16, device=device)

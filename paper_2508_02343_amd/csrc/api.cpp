@@ -123,7 +123,9 @@ mm_status quantize(const void* x, int64_t ldx, const int32_t* perm, const mm_mx_
   a.gamma = static_cast<const uint16_t*>(gamma);
   a.eps = eps;
   a.inv_k = 1.0 / (double)out->K;
-  hipError_t e = mm::launch_quantize(a, static_cast<hipStream_t>(stream));
+  mm::Device dev;
+  hipError_t e = mm::current_device(&dev);
+  if (e == hipSuccess) e = mm::launch_quantize(a, dev, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(MM_ERR_DEVICE, "%s: launch failed: %s", who, hipGetErrorString(e));
   return MM_OK;
 }
@@ -174,15 +176,15 @@ mm::Operand operand(const mm_mx_tensor* t) {
 }
 
 hipError_t launch_gemm(const mm::GemmArgs& g, hipStream_t s) {
-  mm::GemmSizes z = {g.x.rows, g.w.rows, {g.steps[0], g.steps[1], g.steps[2]}, 0};
-  hipError_t e = mm::device_cus(&z.cus);
+  mm::Device dev;
+  hipError_t e = mm::current_device(&dev);
   if (e != hipSuccess) return e;
-  const mm::GemmRoute r = mm::gemm_route(z);
+  const mm::GemmRoute r = mm::gemm_route({g.x.rows, g.w.rows, {g.steps[0], g.steps[1], g.steps[2]}, dev.cus});
   switch (r.kernel) {
-    case mm::GemmKernel::kDirect: return mm::launch_gemm_direct(g, s);
-    case mm::GemmKernel::kSplit: return mm::launch_gemm_split(g, r.shape, s);
-    case mm::GemmKernel::kTiled128: return mm::launch_gemm_tiled(g, false, s);
-    case mm::GemmKernel::kTiled256: return mm::launch_gemm_tiled(g, true, s);
+    case mm::GemmKernel::kDirect: return mm::launch_gemm_direct(g, dev, s);
+    case mm::GemmKernel::kSplit: return mm::launch_gemm_split(g, r.shape, dev, s);
+    case mm::GemmKernel::kTiled128: return mm::launch_gemm_tiled(g, false, dev, s);
+    case mm::GemmKernel::kTiled256: return mm::launch_gemm_tiled(g, true, dev, s);
   }
   return hipErrorInvalidValue;
 }
@@ -191,26 +193,23 @@ hipError_t launch_gemm(const mm::GemmArgs& g, hipStream_t s) {
 
 namespace mm {
 
-hipError_t device_cus(int* cus) {
-  thread_local int last_dev = -1, last_cus = 0;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+hipError_t current_device(Device* d) {
+  thread_local Device last = {-1, 0};
+  int id = 0;
+  hipError_t e = hipGetDevice(&id);
   if (e != hipSuccess) return e;
-  if (dev != last_dev) {
-    e = hipDeviceGetAttribute(&last_cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (id != last.id) {
+    e = hipDeviceGetAttribute(&last.cus, hipDeviceAttributeMultiprocessorCount, id);
     if (e != hipSuccess) return e;
-    last_dev = dev;
+    last.id = id;
   }
-  *cus = last_cus;
+  *d = last;
   return hipSuccess;
 }
 
-hipError_t allow_lds(DeviceOnce& once, const void* kernel, int bytes) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
+hipError_t allow_lds(DeviceOnce& once, const Device& dev, const void* kernel, int bytes) {
   return (hipError_t)once.run(
-      dev, [&] { return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+      dev.id, [&] { return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
 }
 
 }  // namespace mm

@@ -178,11 +178,8 @@ static hipError_t launch_direct_tm(const GemmArgs& a, int R, hipStream_t stream)
 // x N, weights from HBM): 40 x 14336 x 10240 E4M3 30.6 / 40.8, 40 x 8192 x 6144 E4M3
 // 13.9 / 18.4, 33 x 14336 x 6144 mixed 16.7 / 19.3; but 64 x 4096 x 28672 mixed
 // 22.4 / 20.4, 64 x 14336 x 1024 E3M2 19.3 / 14.7.
-hipError_t launch_gemm_direct(const GemmArgs& a, hipStream_t stream) {
-  int cus = 0;
-  hipError_t e = device_cus(&cus);
-  if (e != hipSuccess) return e;
-  const DirectPlan p = direct_plan(a.x.rows, a.w.rows, cus);
+hipError_t launch_gemm_direct(const GemmArgs& a, const Device& dev, hipStream_t stream) {
+  const DirectPlan p = direct_plan(a.x.rows, a.w.rows, dev.cus);
   if (a.x.rows <= 16) return p.waves == 4 ? launch_direct<2, 1, 4>(a, p.rows, stream) : launch_direct<1, 1, 8>(a, p.rows, stream);
   return a.x.rows <= 32 ? launch_direct_tm<2>(a, p.rows, stream) : launch_direct_tm<4>(a, p.rows, stream);
 }

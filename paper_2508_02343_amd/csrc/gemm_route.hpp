@@ -32,10 +32,10 @@ inline void share_waves(const int* steps, const int* cost, int W, int* w) {
   for (int G = 0; G < 3; ++G) w[G] = steps[G] > 0 ? 1 : 0;
   for (int k = w[0] + w[1] + w[2]; k < W && k > 0; ++k) {
     int best = -1;
-    int64_t most = -1;
+    int most = -1;
     for (int G = 2; G >= 0; --G) {
       if (w[G] == 0) continue;
-      const int64_t c = ceil_div(steps[G], w[G]) * cost[G];
+      const int c = (steps[G] + w[G] - 1) / w[G] * cost[G];  // (at most 2^23 steps)
       if (c > most) {
         most = c;
         best = G;
@@ -140,7 +140,7 @@ inline double longest_chain(const int* steps, const int* cost, int W, const doub
   double most = 0;
   for (int G = 0; G < 3; ++G) {
     if (!steps[G]) continue;
-    const double c = (double)ceil_div(steps[G], w[G]) * time[G];
+    const double c = (steps[G] + w[G] - 1) / w[G] * time[G];
     most = c > most ? c : most;
   }
   return most;

@@ -354,10 +354,10 @@ __global__ __launch_bounds__(kThreads) void gemm_split_kernel(GemmArgs a, int ti
 }
 
 template <int TN, int TM, int FS>
-static hipError_t launch_split_fs(const GemmArgs& a, hipStream_t stream) {
+static hipError_t launch_split_fs(const GemmArgs& a, const Device& dev, hipStream_t stream) {
   constexpr int lds = lds_bytes<TN, TM>();
   static DeviceOnce once;
-  hipError_t e = allow_lds(once, reinterpret_cast<const void*>(gemm_split_kernel<TN, TM, FS>), lds);
+  hipError_t e = allow_lds(once, dev, reinterpret_cast<const void*>(gemm_split_kernel<TN, TM, FS>), lds);
   if (e != hipSuccess) return e;
   const int64_t tn = (a.w.rows + 32 * TN - 1) / (32 * TN), tm = (a.x.rows + 32 * TM - 1) / (32 * TM);
   int w[3];
@@ -369,28 +369,28 @@ static hipError_t launch_split_fs(const GemmArgs& a, hipStream_t stream) {
 
 // The format set is an instruction immediate: one kernel per set.
 template <int TN, int TM>
-static hipError_t launch_split(const GemmArgs& a, hipStream_t stream) {
+static hipError_t launch_split(const GemmArgs& a, const Device& dev, hipStream_t stream) {
   switch (a.fs) {
-    case 0: return launch_split_fs<TN, TM, 0>(a, stream);
-    case 1: return launch_split_fs<TN, TM, 1>(a, stream);
-    case 2: return launch_split_fs<TN, TM, 2>(a, stream);
-    case 3: return launch_split_fs<TN, TM, 3>(a, stream);
+    case 0: return launch_split_fs<TN, TM, 0>(a, dev, stream);
+    case 1: return launch_split_fs<TN, TM, 1>(a, dev, stream);
+    case 2: return launch_split_fs<TN, TM, 2>(a, dev, stream);
+    case 3: return launch_split_fs<TN, TM, 3>(a, dev, stream);
   }
   return hipErrorInvalidValue;
 }
 
 template <int I>
-static hipError_t launch_shape(const GemmArgs& a, hipStream_t stream) {
-  return launch_split<kSplitShapes[I].tn, kSplitShapes[I].tm>(a, stream);
+static hipError_t launch_shape(const GemmArgs& a, const Device& dev, hipStream_t stream) {
+  return launch_split<kSplitShapes[I].tn, kSplitShapes[I].tm>(a, dev, stream);
 }
 
-hipError_t launch_gemm_split(const GemmArgs& a, int shape, hipStream_t stream) {
+hipError_t launch_gemm_split(const GemmArgs& a, int shape, const Device& dev, hipStream_t stream) {
   switch (shape) {
-    case 0: return launch_shape<0>(a, stream);
-    case 1: return launch_shape<1>(a, stream);
-    case 2: return launch_shape<2>(a, stream);
-    case 3: return launch_shape<3>(a, stream);
-    case 4: return launch_shape<4>(a, stream);
+    case 0: return launch_shape<0>(a, dev, stream);
+    case 1: return launch_shape<1>(a, dev, stream);
+    case 2: return launch_shape<2>(a, dev, stream);
+    case 3: return launch_shape<3>(a, dev, stream);
+    case 4: return launch_shape<4>(a, dev, stream);
   }
   return hipErrorInvalidValue;
 }

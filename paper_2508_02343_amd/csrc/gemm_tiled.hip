@@ -771,9 +771,9 @@ __global__ __launch_bounds__((Tile<BN, BM>::kThreads), 1) void gemm_tiled_kernel
 }
 
 template <int BN, int BM, int FS>
-static hipError_t launch_tile_fs(const GemmArgs& a, hipStream_t stream) {
+static hipError_t launch_tile_fs(const GemmArgs& a, const Device& dev, hipStream_t stream) {
   static DeviceOnce once;
-  hipError_t e = allow_lds(once, reinterpret_cast<const void*>(gemm_tiled_kernel<BN, BM, FS>), kLdsBytes);
+  hipError_t e = allow_lds(once, dev, reinterpret_cast<const void*>(gemm_tiled_kernel<BN, BM, FS>), kLdsBytes);
   if (e != hipSuccess) return e;
   const int tn = (int)((a.w.rows + BN - 1) / BN), tm = (int)((a.x.rows + BM - 1) / BM);
   hipLaunchKernelGGL((gemm_tiled_kernel<BN, BM, FS>), dim3((unsigned)(tn * tm)), dim3(Tile<BN, BM>::kThreads), kLdsBytes, stream, a,
@@ -783,18 +783,18 @@ static hipError_t launch_tile_fs(const GemmArgs& a, hipStream_t stream) {
 
 // The format set is an instruction immediate: one kernel per set.
 template <int BN, int BM>
-static hipError_t launch_tile(const GemmArgs& a, hipStream_t stream) {
+static hipError_t launch_tile(const GemmArgs& a, const Device& dev, hipStream_t stream) {
   switch (a.fs) {
-    case 0: return launch_tile_fs<BN, BM, 0>(a, stream);
-    case 1: return launch_tile_fs<BN, BM, 1>(a, stream);
-    case 2: return launch_tile_fs<BN, BM, 2>(a, stream);
-    case 3: return launch_tile_fs<BN, BM, 3>(a, stream);
+    case 0: return launch_tile_fs<BN, BM, 0>(a, dev, stream);
+    case 1: return launch_tile_fs<BN, BM, 1>(a, dev, stream);
+    case 2: return launch_tile_fs<BN, BM, 2>(a, dev, stream);
+    case 3: return launch_tile_fs<BN, BM, 3>(a, dev, stream);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm_tiled(const GemmArgs& a, bool square, hipStream_t stream) {
-  return square ? launch_tile<256, 256>(a, stream) : launch_tile<256, 128>(a, stream);
+hipError_t launch_gemm_tiled(const GemmArgs& a, bool square, const Device& dev, hipStream_t stream) {
+  return square ? launch_tile<256, 256>(a, dev, stream) : launch_tile<256, 128>(a, dev, stream);
 }
 
 }  // namespace mm

@@ -95,21 +95,26 @@ struct CalibArgs {
 // to K = 31488 channels, whatever the number of rows.
 constexpr int64_t kCalibScratchBytes = 16ll << 20;
 
-hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream);
+// The current device (cached per thread for the last one), looked up once per call.
+struct Device {
+  int id, cus;
+};
+hipError_t current_device(Device* d);
+
+hipError_t launch_quantize(const QuantArgs& a, const Device& dev, hipStream_t stream);
 hipError_t launch_calibrate(const CalibArgs& a, hipStream_t stream);
 // Device address of the current device's calibration scratch: looked up
 // with hipGetSymbolAddress on the first call on each device, with that
 // device current, and cached per device.  Allocates nothing.
 hipError_t calibrate_scratch(void** ptr);
-hipError_t launch_gemm_direct(const GemmArgs& a, hipStream_t stream);  // at most 64 activation rows
-hipError_t launch_gemm_tiled(const GemmArgs& a, bool square, hipStream_t stream);  // 256 x 256 tiles, else 256 x 128
+hipError_t launch_gemm_direct(const GemmArgs& a, const Device& dev, hipStream_t stream);  // at most 64 activation rows
+// 256 x 256 tiles, else 256 x 128
+hipError_t launch_gemm_tiled(const GemmArgs& a, bool square, const Device& dev, hipStream_t stream);
 // The K-splitting kernel with a tile shape (an index into kSplitShapes) whose
 // rows the padded operands have.
-hipError_t launch_gemm_split(const GemmArgs& a, int shape, hipStream_t stream);
-// CUs of the current device (cached per thread for the last device).
-hipError_t device_cus(int* cus);
-// Lets a kernel have this much dynamic LDS on the current device (`once`: the
-// kernel's own).
-hipError_t allow_lds(DeviceOnce& once, const void* kernel, int bytes);
+hipError_t launch_gemm_split(const GemmArgs& a, int shape, const Device& dev, hipStream_t stream);
+// Lets a kernel have this much dynamic LDS on the device, the current one
+// (`once`: the kernel's own).
+hipError_t allow_lds(DeviceOnce& once, const Device& dev, const void* kernel, int bytes);
 
 }  // namespace mm

@@ -508,13 +508,10 @@ __global__ __launch_bounds__(kMaxThreads) void quantize_kernel(QuantArgs a) {
 }
 
 template <int RH, bool kNorm>
-static hipError_t launch_rows(const QuantArgs& a, hipStream_t stream) {
+static hipError_t launch_rows(const QuantArgs& a, const Device& dev, hipStream_t stream) {
   static DeviceOnce once;
   constexpr int kLds = 160 * 1024;
-  hipError_t e = allow_lds(once, reinterpret_cast<const void*>(quantize_kernel<RH, kNorm>), kLds);
-  if (e != hipSuccess) return e;
-  int cus = 0;
-  e = device_cus(&cus);
+  hipError_t e = allow_lds(once, dev, reinterpret_cast<const void*>(quantize_kernel<RH, kNorm>), kLds);
   if (e != hipSuccess) return e;
   const int waves = (RH * (a.K >> 5) + 63) / 64;
   const size_t lds = (size_t)RH * (2 * a.K + 16) + (kNorm ? 2 * (size_t)a.K + 8 * (kMaxThreads / 64) * RH : 0);
@@ -527,7 +524,7 @@ static hipError_t launch_rows(const QuantArgs& a, hipStream_t stream) {
   // 20.8; 28557 x 2272 48.8 -> 39.3 us).
   int64_t per = waves <= 4 ? 16 / waves : 4 / ((waves + 3) / 4);
   if (per * lds > kLds) per = kLds / lds;
-  const int64_t passes = (a.rp + RH - 1) / RH, cap = per * cus;
+  const int64_t passes = (a.rp + RH - 1) / RH, cap = per * dev.cus;
   hipLaunchKernelGGL((quantize_kernel<RH, kNorm>), dim3((unsigned)(passes < cap ? passes : cap)), dim3(64 * waves), lds,
                      stream, a);
   return hipGetLastError();
@@ -550,16 +547,13 @@ static hipError_t launch_rows(const QuantArgs& a, hipStream_t stream) {
 // (K 4128 .. 5120: one row makes five of three, 28557 x 5120 125 -> 118, 8192 x
 // 5120 42.3 -> 40.9, but only from 4480 channels on, which fill most of their
 // lanes: 28557 x 4160 112 -> 121).
-hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream) {
+hipError_t launch_quantize(const QuantArgs& a, const Device& dev, hipStream_t stream) {
   if (a.rows == 0) return hipSuccess;
   const bool norm = a.norm != 0;
   const int64_t n = a.rp * a.K;
   int rh = a.K <= 8192 ? 4 : (a.K <= 16384 ? 2 : 1);
   if (a.K >= 2048) {
-    int cus = 0;
-    hipError_t e = device_cus(&cus);
-    if (e != hipSuccess) return e;
-    if (n < (1 << 20) || (a.K > 8192 && a.rp <= cus)) rh = 1;
+    if (n < (1 << 20) || (a.K > 8192 && a.rp <= dev.cus)) rh = 1;
     else if (n < (24 << 20) && rh > 2) rh = 2;
     else if (norm && a.K > 2048 && a.K <= 2560) rh = 2;
     else if (norm && a.K >= 4480 && a.K <= 5120) rh = 1;
@@ -567,10 +561,10 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream) {
     rh = 16;
   }
   switch (rh) {
-    case 1: return norm ? launch_rows<1, true>(a, stream) : launch_rows<1, false>(a, stream);
-    case 2: return norm ? launch_rows<2, true>(a, stream) : launch_rows<2, false>(a, stream);
-    case 4: return norm ? launch_rows<4, true>(a, stream) : launch_rows<4, false>(a, stream);
-    default: return launch_rows<16, false>(a, stream);
+    case 1: return norm ? launch_rows<1, true>(a, dev, stream) : launch_rows<1, false>(a, dev, stream);
+    case 2: return norm ? launch_rows<2, true>(a, dev, stream) : launch_rows<2, false>(a, dev, stream);
+    case 4: return norm ? launch_rows<4, true>(a, dev, stream) : launch_rows<4, false>(a, dev, stream);
+    default: return launch_rows<16, false>(a, dev, stream);
   }
 }
 
