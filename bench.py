@@ -51,7 +51,7 @@ def quant_bytes(rows: int, K: int, split) -> int:
     return rows * K * 2 + rows * (p4 // 2 + 3 * p6 // 4 + p8) + rows * K // 32 + 4 * K
 
 
-DIRECT_MAX_M = 64  # up to this many activation rows mm_gemm is bound by the weight stream from HBM
+HBM_BOUND_M = 64  # up to this many activation rows mm_gemm is bound by the weight stream from HBM
 
 
 def gemm_bytes(M: int, N: int, K: int, split) -> int:
@@ -62,8 +62,8 @@ def gemm_bytes(M: int, N: int, K: int, split) -> int:
     return M * row + N * row + M * N * 2
 
 
-# sources each GEMM kernel is compiled from (a committed counter summary is
-# used only while they are unchanged)
+# sources the GEMM kernels above ("tiled") and up to that many rows ("direct") are
+# compiled from (a committed counter summary is used only while they are unchanged)
 GEMM_SOURCES = {"tiled": ("gemm_tiled.hip", "gemm_common.hpp", "mx_device.hpp", "kernels.hpp"),
                 "direct": ("gemm_direct.hip", "gemm_split.hip", "gemm_route.hpp", "gemm_common.hpp", "mx_device.hpp",
                            "kernels.hpp")}
@@ -94,7 +94,7 @@ def _profile_entry(fname: str, workload: str):
         return None
     from paper_2508_02343_amd import workloads as W
 
-    kind = "direct" if W.BY_NAME[workload].M <= DIRECT_MAX_M else "tiled"
+    kind = "direct" if W.BY_NAME[workload].M <= HBM_BOUND_M else "tiled"
     if entry.get("source_hash") != gemm_source_hash(kind):
         return None
     return entry
@@ -225,7 +225,7 @@ class Operands:
         gemm_set = w.M * row + w.N * row + w.M * w.N * 2
         # (a decode step's activation is a few KB, read from cache whatever
         # the rotation: there the GEMM's weight stream sets the count)
-        touched = min(quant_set, gemm_set) if w.M > DIRECT_MAX_M else gemm_set
+        touched = min(quant_set, gemm_set) if w.M > HBM_BOUND_M else gemm_set
         self.nbuf = n = max(1, int(np.ceil(min_set_mb * 1e6 / touched)))
         self.X = [x0] + [x0.clone() for _ in range(n - 1)]
         self.XQ = [B.MXTensor.empty(w.M, w.K, w.split, device=dev) for _ in range(n)]
@@ -354,9 +354,9 @@ def norm_stats(B, W, ops, dev, stream, n: int, quant_ms: float) -> dict:
 
 def gemm_roofline(w, mean_ms: float, median_ms: float) -> dict:
     """The GEMM against its roofline: the bit mix's MFMA peak for prefill
-    shapes, HBM for the decode kernel (M <= 64)."""
+    shapes, HBM up to HBM_BOUND_M rows."""
     flops = 2.0 * w.M * w.N * w.K
-    if w.M > DIRECT_MAX_M:
+    if w.M > HBM_BOUND_M:
         ach = flops / (mean_ms * 1e-3) / 1e12
         peak = mix_peak_tflops(w.split)
         r = {"bound": "mfma", "kernel": "mixed MX GEMM", "achieved": round(ach, 2), "peak": round(peak, 1),
@@ -370,7 +370,7 @@ def gemm_roofline(w, mean_ms: float, median_ms: float) -> dict:
              "unit": "GB/s", "frac": round(ach / PEAK_HBM, 4),
              "median_frac": round(nbytes / (median_ms * 1e-3) / 1e9 / PEAK_HBM, 4)}
     r.update({"traffic": measured_traffic(w.name), "ms": round(mean_ms, 5), "median_ms": round(median_ms, 5),
-              "source_hash": gemm_source_hash("direct" if w.M <= DIRECT_MAX_M else "tiled")})
+              "source_hash": gemm_source_hash("direct" if w.M <= HBM_BOUND_M else "tiled")})
     return r
 
 
@@ -499,7 +499,7 @@ def main() -> int:
                 "rmsnorm_quantizer": {k: nrm[k] for k in ("ms", "frac", "vs_plain_quantizer", "unfused_pair_ms")}}
 
     sweep = None
-    if not args.no_sweep and w.M > DIRECT_MAX_M:
+    if not args.no_sweep and w.M > HBM_BOUND_M:
         # the other prefill shapes, each kernel timed the same way
         sweep = []
         for wl in W.PREFILL:

@@ -48,12 +48,13 @@
 // XCD by XCD and in groups of weight tiles, so the tiles that run together
 // on one XCD share its L2.
 //
-// Measured (us, M x N x K): without the producers and with the waits between
-// the stages 2048 x 4096 x 4096 took 29.9 (now 27.0), 1000 x 4096 x 5400 in
+// Measured (us, M x K x N): without the producers and with the waits between
+// the stages 2048 x 4096 x 4096 took 29.9 (with them 27.0), 1000 x 4096 x 5400 in
 // E2M3 / E5M2 30.1 (26.6), 700 x 4096 x 14336 44.0 (39.4); the 256 x 256 tile
-// 4096 x 4096 x 14336 150 (148.5), 8192 x 5120 x 27648 640 (636): that one is
-// at the card's power limit (all-zero codes: 507).  The MFMAs alone, without
-// loads and LDS reads: 19.0 (2048 x 4096 x 4096), 430 (8192 x 5120 x 27648).
+// 4096 x 4096 x 14336 150 (148.5), 8192 x 5120 x 27648 640 (636; with all-zero
+// codes 507: power is a part of what bounds it).  Without loads and LDS reads,
+// but with the launch, the set-up and the epilogue of every tile: 19.0 (2048 x
+// 4096 x 4096, of which the K loop's MFMAs are 9-10), 430 (8192 x 5120 x 27648).
 #include "gemm_common.hpp"
 
 namespace mm {
@@ -507,9 +508,9 @@ __device__ __forceinline__ void mfma_block(const Ctx<BN, BM>& c, Acc<BN, BM>& ac
 // l.st is its slot; on exit the same holds for the next group's.  The first
 // MFMAs need the second stage as well: it has landed behind the barrier in
 // front of them.  The cursor is pointed while the first stage's reads run;
-// behind the barrier it held a tile's first MFMAs back by 0.3-0.4 us (us, M x N
-// x K: 768 x 22016 x 128 in E2M1 19.0 -> 18.0, 8192 x 28672 x 128 132.5 -> 127.5,
-// 4096 x 14336 x 4096 149.4 -> 146.4).
+// behind the barrier it held a tile's first MFMAs back by 0.3-0.4 us (us, M x K
+// x N: 768 x 128 x 22016 in E2M1 19.0 -> 18.0, 8192 x 128 x 28672 132.5 -> 127.5,
+// 4096 x 4096 x 14336 149.4 -> 146.4).
 template <int G, int FS, int BN, int BM>
 __device__ __forceinline__ void run_group(const Ctx<BN, BM>& c, Acc<BN, BM>& acc, Loop<BN, BM>& l) {
   using T = Tile<BN, BM>;

@@ -38,14 +38,15 @@
 // workgroup per CU, and for K > 8192 one row per workgroup at a time):
 //   plain   8 x 4096   5.2 -> 3.7    2048 x 4096  9.3 ->  8.5   8192 x 5120   30.7 -> 25.1 (4.4 TB/s)
 //         333 x 27648 19.4 -> 13.3   4096 x 14336 39.5 -> 34.0   5120 x 27648 170  -> 86
-//   norm    8 x 4096   8.6 -> 5.2    2048 x 4096 13.8 -> 12.8   8192 x 5120   43.4 -> 41.4
+//   norm    8 x 4096   8.6 -> 5.2    2048 x 4096 13.8 -> 12.8   8192 x 5120   43.4 -> 40.9
 //         512 x 4096   9.1 -> 6.5    4096 x 14336 73.3 -> 50.4   5120 x 27648 577  -> 113
 // The plain kernel waits on memory (loads in flight only while a workgroup
 // quantises, code stores in runs of a few rows); the norm's 540 VALU
 // instructions per wavefront and pass, against 190, bound its large shapes.
-// What spills costs more than what it saves: 128 registers hold the norm
-// variant only because it gathers eight channels at a time (with 32 spilled
-// registers 8192 x 5120 took 59 us, with 10, 44).  Tried: two blocks per thread
+// What spills costs more than what it saves: the norm variant fits 128 registers
+// only because it gathers eight channels at a time (with 32 spilled registers
+// 8192 x 5120 took 59 us, with 10, 44); with two and four rows per pass it still
+// spills two.  Tried: two blocks per thread
 // (34 us plain on 8192 x 5120), five wavefronts per SIMD (spills, 37 us).
 #include "kernels.hpp"
 
