@@ -86,16 +86,16 @@ constexpr int kNumSplitShapes = sizeof(kSplitShapes) / sizeof(kSplitShapes[0]);
 
 // ---- the choice: the kernel with the least estimated time ----
 //
-// Estimates in us, fitted to 4500 sizes (1 .. 8192 x 128 .. 27648 x 512 .. 28672,
+// Estimates in us, fitted to 8000 sizes (1 .. 8192 x 128 .. 27648 x 512 .. 28672,
 // E2M1, E3M2, E4M3 and mixed splits) on 256 CUs with the weights in rotation
-// beyond the caches, as replays of a captured graph: within 6 % (K-splitting and
-// tiled kernels) and 9 % (decode kernel) in the mean square.  With weights that
+// beyond the caches, as replays of a captured graph: within 4-9 % (K-splitting and
+// tiled kernels) and 8-10 % (decode kernel) in the mean square.  With weights that
 // stay in the cache, as the rule before this one was fitted, the K-splitting
 // kernel looks up to 1.6 times faster than it is in a model.  Against every
-// kernel measured at these sizes the choice is 0.4 % slower than the best in the
-// mean; the former rule was 7 % slower, worst (us, the former choice / now, M x
-// K x N): 8192 x 128 x 14336 E2M1 212 / 66, 24 x 27648 x 4096 E2M1 21.8 / 15.1,
-// 8 x 27648 x 4096 mixed 26.6 / 16.1.
+// kernel measured at these and 3100 more sizes the choice is 0.6 % slower than the
+// best in the mean; the former rule was 7 % slower, worst (us, the former choice /
+// now, M x K x N): 8192 x 128 x 14336 E2M1 212 / 66, 24 x 27648 x 4096 E2M1 21.8 /
+// 15.1, 8 x 27648 x 4096 mixed 26.6 / 16.1.
 //
 // A kernel's time is a sum over the parts that bound it at some sizes: its
 // launch, the rounds of tiles over the CUs, in each round the longest chain of
@@ -109,30 +109,32 @@ struct GemmCost {
   double w, x, y;  // per 2^20 bytes of weight, activation and result
 };
 constexpr GemmCost kSplitCost[kNumSplitShapes] = {
-    {2.46, 0.21, 0.038, 0.0566, 0.090, 0, 0.32},  {2.51, 0.29, 0.054, 0.0602, 0.113, 0.105, 0.47},
-    {1.73, 1.74, 0, 0.1073, 0.092, 0.084, 0.23},  {1.63, 2.34, 0.158, 0.1164, 0.103, 0.138, 0.26},
-    {1.48, 3.39, 0.107, 0.1268, 0.125, 0.48, 0.16}};
-constexpr GemmCost kTiled128Cost = {4.54, 0.20, 0, 0.422, 0.062, 0, 0.245};
-constexpr GemmCost kTiled256Cost = {0, 9.22, 0, 0.583, 0.084, 0.157, 0};
+    {2.68, 0.0429, 0.0528, 0.0549, 0.084, 0.143, 0.549}, {2.83, 0.0739, 0.0388, 0.0684, 0.102, 0, 0.594},
+    {1.79, 1.73, 0, 0.112, 0.0859, 0.0276, 0.195}, {1.32, 2.81, 0, 0.125, 0.11, 0.238, 0.247},
+    {1.51, 3.58, 0.0783, 0.132, 0.12, 0.424, 0.0965}};
+constexpr GemmCost kTiled128Cost = {4.74, 0, 0, 0.42, 0.0564, 0, 0.256};
+constexpr GemmCost kTiled256Cost = {0, 9.2, 0, 0.583, 0.0828, 0.158, 0.00553};
 
 // The decode kernel's rounds are strips per CU, at least one, without rounding
-// up (several run on a CU at a time); with one, two or four activation tiles.
+// up (several run on a CU at a time); with one activation tile and 16 or 32 weight
+// rows per workgroup, with two and with four activation tiles.
 struct DirectCost {
   double once, round;
   double chain, chain_m, chain_n;  // per round and step of the longest chain: fixed, per 16 activation rows, per 16 weight rows
   double w, y;
 };
-constexpr DirectCost kDirectCost[3] = {
-    {2.13, 0.30, 0.139, 0.0358, 0, 0.110, 0.11}, {0.76, 1.40, 0.239, 0, 0.020, 0.120, 2.34}, {0, 2.73, 0.019, 0.0965, 0.110, 0.063, 1.66}};
+constexpr DirectCost kDirectCost[4] = {
+    {2.32, 0, 0, 0.0509, 0.17, 0.111, 0.0414}, {2.76, 0.153, 0, 0.00368, 0.00246, 0.188, 0.306},
+    {0.631, 1.82, 0.23, 0, 0, 0.134, 2.08}, {0, 2.88, 0.0375, 0.0936, 0.0649, 0.0853, 1.44}};
 
 // A step's time in the estimates: E2M1 1.  E3M2 codes are 24 bytes per lane and
 // block: two loads (K-splitting kernel), three (decode kernel).
 constexpr double kStepTime[3] = {1, 27.0 / 17, 33.0 / 17}, kDirectStepTime[3] = {1, 2, 33.0 / 17};
 
 // The estimates scatter by a few percent: between near equals the decode kernel
-// (up to kDirectMaxM rows) and the tiled one are taken, whose loads are the
-// more even.
-constexpr double kSplitHandicap = 1.05;
+// (up to kDirectMaxM rows) and the tiled one (above) are taken.  Without the
+// handicap five times as many of the 11100 sizes lose more than 3 % to them.
+constexpr double kHandicap = 1.06;
 
 inline double longest_chain(const int* steps, const int* cost, int W, const double* time) {
   int w[3];
@@ -159,18 +161,19 @@ inline GemmRoute gemm_route(const GemmSizes& a) {
     const double rounds = (double)ceil_div(tile_count(a.n, a.m, tn, tm), a.cus);
     return c.once + rounds * (c.round + c.chain * chain + c.step * steps) + c.w * w + c.x * x + c.y * y;
   };
+  const double tiled = a.m <= kDirectMaxM ? kHandicap : 1.0;
   GemmRoute best = {GemmKernel::kTiled256, 0};
-  double least = cost(kTiled256Cost, 8, 8);
+  double least = tiled * cost(kTiled256Cost, 8, 8);
   auto offer = [&](double c, GemmRoute r, int64_t threads) {
     if (threads < kMaxThreads && c < least) {
       least = c;
       best = r;
     }
   };
-  offer(cost(kTiled128Cost, 8, 4), {GemmKernel::kTiled128, 0}, tile_count(a.n, a.m, 8, 4) * 512);
+  offer(tiled * cost(kTiled128Cost, 8, 4), {GemmKernel::kTiled128, 0}, tile_count(a.n, a.m, 8, 4) * 512);
   if (a.m <= kDirectMaxM) {
     const DirectPlan p = direct_plan(a.m, a.n, a.cus);
-    const DirectCost& c = kDirectCost[a.m <= 16 ? 0 : (a.m <= 32 ? 1 : 2)];
+    const DirectCost& c = kDirectCost[a.m <= 16 ? (p.waves == 8 ? 0 : 1) : (a.m <= 32 ? 2 : 3)];
     const int64_t strips = ceil_div(a.n, p.rows);
     const double rounds = strips > a.cus ? (double)strips / a.cus : 1.0;
     const double per_step = c.chain + c.chain_m * (double)a.m / 16 + c.chain_n * p.rows / 16;
@@ -180,7 +183,7 @@ inline GemmRoute gemm_route(const GemmSizes& a) {
   for (int i = 0; i < kNumSplitShapes; ++i) {
     const SplitShape& s = kSplitShapes[i];
     if (32 * s.tn > rn || 32 * s.tm > rm) continue;  // the operands have not so many rows
-    offer(kSplitHandicap * cost(kSplitCost[i], s.tn, s.tm), {GemmKernel::kSplit, i}, tile_count(a.n, a.m, s.tn, s.tm) * 512);
+    offer(kHandicap * cost(kSplitCost[i], s.tn, s.tm), {GemmKernel::kSplit, i}, tile_count(a.n, a.m, s.tn, s.tm) * 512);
   }
   return best;
 }

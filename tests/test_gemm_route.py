@@ -33,6 +33,10 @@ MEASURED = [
     (32, 6144, _mix(14336), {D: 14.8, S1: 16.1, S2: 20.5}),
     (17, 6144, (14336, 0, 0), {D: 12.1, S1: 15.0, S2: 18.1}),
     (1, 4096, (0, 14336, 0), {D: 11.1, S1: 18.2, S2: 24.0}),
+    # one activation tile, whole row groups: every CU streams at the memory's rate
+    (16, 24411, (2560, 1280, 1280), {D: 18.1, S1: 20.6, S2: 21.1}),
+    (8, 18290, (4128, 832, 3232), {D: 24.9, S1: 28.0, S2: 29.3}),
+    (16, 16852, (1024, 160, 864), {D: 8.7, S1: 9.8, S2: 10.1}),
     # two activation tiles against many weight rows of few channels
     (32, 28672, (1024, 0, 0), {D: 8.4, S1: 7.2, S2: 6.7, T1: 9.3}),
     # four activation tiles: 8-bit codes and long K on the decode kernel
