@@ -230,7 +230,11 @@ class MXTensor:
 def _check_mx(t: MXTensor, rows: int, K: int, split, device, name: str) -> None:
     """An MXTensor whose buffers hold the packed layout of (rows, K, split)
     on `device` (the library reads and writes exactly those bytes)."""
-    split = tuple(map(int, split))
+    _check_layout(t, rows, K, tuple(map(int, split)), device, name)
+
+
+def _check_layout(t: MXTensor, rows: int, K: int, split: tuple, device, name: str) -> None:
+    """The same for a split of ints."""
     if t.rows != rows or t.K != K or tuple(map(int, t.split)) != split:
         raise ValueError(f"{name} is [{t.rows}, {t.K}] split {tuple(t.split)}, expected [{rows}, {K}] split "
                          f"{split}")
@@ -238,6 +242,7 @@ def _check_mx(t: MXTensor, rows: int, K: int, split, device, name: str) -> None:
 
 
 def _check_buffers(t: MXTensor, rows: int, K: int, split: tuple, device, name: str) -> None:
+    """The same for a tensor that says it has that layout."""
     index = -1 if device.type == "cpu" else device.index  # (comparing devices costs four times as much)
     for b, buf, need in zip(("q4", "q6", "q8", "sc"), (t.q4, t.q6, t.q8, t.sc), _buffer_sizes(rows, K, split)):
         n = 0 if buf is None else buf.nbytes
@@ -259,7 +264,7 @@ def _quantize(fn, x: torch.Tensor, perm: torch.Tensor, split, out: MXTensor | No
     if out is None:
         out = MXTensor.empty(rows, K, split, device=device, formats=formats)
     else:
-        _check_mx(out, rows, K, split, device, "out")
+        _check_layout(out, rows, K, split, device, "out")
     _check(fn(x.data_ptr(), x.stride(0), *norm, perm.data_ptr(), out._packed(), _stream_int(stream)))
     return out
 
